@@ -17,7 +17,7 @@ CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libchfsi.so")
 BUILD_DIR = os.path.join(HERE, "_build")
 
-SOURCES = ["op_build.cpp", "api.cpp", "mlp.cpp", "kernels_hx.hip", "kernels_nl.hip", "kernels_density.hip",
+SOURCES = ["op_build.cpp", "api.cpp", "mlp.cpp", "kernels_hx.hip", "kernels_tensor.hip", "kernels_nl.hip", "kernels_density.hip",
            "kernels_dense.hip", "kernels_mlp.hip", "kernels_dhm.hip",
            "kernels_scf.hip", "kernels_small.hip"]
 

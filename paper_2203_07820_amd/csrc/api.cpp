@@ -102,6 +102,14 @@ int build_colours(chfsi_op* op) {
   return 0;
 }
 
+// In the deterministic mode: refuses an operator without colour classes.
+int deterministic_ready(chfsi_op* op) {
+  chfsi_ctx* ctx = op->ctx;
+  if (!ctx->deterministic || op->colour_cells) return 0;
+  if (op->t.ncell < 2) CHECK(build_colours(op));   // fails with the reason
+  return fail(ctx, CHFSI_EINVAL, "colour classes of the operator are not built");
+}
+
 // One H~.X launch over all cells, or, with deterministic assembly, one per
 // colour class in a fixed order: inside a class every node receives at most
 // one contribution, so each node's sum is formed in the class order
@@ -112,10 +120,7 @@ int launch_hx_cells(chfsi_op* op, const HxLaunch& L, int prec) {
     HIP_TRY(ctx, launch_cell_hx(L, prec, ctx->stream));
     return 0;
   }
-  if (!op->colour_cells) {
-    if (op->t.ncell < 2) CHECK(build_colours(op));   // fails with the reason
-    return fail(ctx, CHFSI_EINVAL, "colour classes of the operator are not built");
-  }
+  CHECK(deterministic_ready(op));
   for (size_t k = 0; k + 1 < op->colour_off.size(); ++k) {
     HxLaunch Lk = L;
     Lk.cells = op->colour_cells + op->colour_off[k];
@@ -241,10 +246,80 @@ double cell_kernel_flops(const chfsi_op* op, int64_t ncols) {
   return fl;
 }
 
-// Y = alpha (H~ Xk - c Xk) - beta Xp  accumulated into T (which must hold 0
-// on entry).  Xk, Xp, T are in the storage type of prec, logical ld.
+// Whether H~.X in `prec` goes through the tensor-product kernel: the cells
+// share one cell matrix (not the per-cell quadrature potential), the products
+// are not the bf16-rounded ones (defined on the dense cell matrix's entries),
+// and a plane of every block stays below 2 GB (the kernel's 32-bit offsets).
+// Else the dense cell kernel takes it.
+bool tensor_path(const chfsi_op* op, int prec, int64_t ldmax) {
+  if (op->astride != 0 || prec == CHFSI_BF16) return false;
+  const int64_t n = op->t.n;
+  return static_cast<double>(n) * n * ldmax * prec_bytes(prec) < 2147483648.0;
+}
+
+// T = alpha (H~ Xk - c Xk) - beta Xp through the tensor-product kernel.
+TensorLaunch make_tensor(const chfsi_op* op, int prec, const void* Xk, int64_t ldx, const void* Xp, int64_t ldp,
+                         void* T, int64_t ldt, int64_t ncols, double alpha, double c, double beta) {
+  const HostTables& t = op->t;
+  const int cf = t.cplx ? 2 : 1;
+  TensorLaunch L;
+  L.p = t.p;
+  L.nc = t.ncell;
+  L.ncols = static_cast<int>(ncols * cf);
+  L.ncu = op->ctx->ncu;
+  L.h = t.h;
+  for (int i = 0; i < 3; ++i) L.kh[i] = t.k[i] * t.h;
+  L.tab = is_single(prec) ? op->ts_tab32 : op->ts_tab64;
+  L.vdiag = op->vdiag;
+  L.Xk = Xk;
+  L.ldx = ldx * cf;
+  L.Xp = Xp;
+  L.ldp = ldp * cf;
+  L.T = T;
+  L.ldt = ldt * cf;
+  L.alpha = alpha;
+  L.c = c;
+  L.beta = beta;
+  return L;
+}
+
+// Nonlocal update Y += alpha C (h P) (and next projection into hP through
+// `part`, nullable) of the tensor-product path.
+NlUpdate make_update(const chfsi_op* op, int prec, void* Y, int64_t ldy, int64_t ncols, double alpha, void* hP,
+                     int64_t ldhp, void* part) {
+  const HostTables& t = op->t;
+  NlUpdate u;
+  u.natoms = t.natoms;
+  u.ncells = op->nown_cells;
+  u.nc = t.ncell;
+  u.ncols = static_cast<int>(ncols);
+  u.nreal = static_cast<int>(ncols * (t.cplx ? 2 : 1));
+  u.cells = op->own_cell;
+  u.pair_ptr = op->own_ptr;
+  u.pair_atom = op->own_atom;
+  u.val = is_single(prec) ? op->own_val32 : op->own_val64;
+  u.atom_pair_ptr = op->atom_pair_ptr;
+  u.atom_pair = op->atom_pair;
+  u.hcoef = op->hcoef;
+  u.Y = Y;
+  u.ldy = ldy;
+  u.alpha = alpha;
+  u.update = 1;
+  u.hP = hP;
+  u.ldhp = ldhp;
+  u.part = part;
+  return u;
+}
+
+// Y = alpha (H~ Xk - c Xk) - beta Xp: stored into T on the tensor-product
+// path (T may be Xp), accumulated into T on the dense one (T must hold 0 on
+// entry).  Xk, Xp, T are in the storage type of prec, logical ld.
+// On the tensor-product path, `projected` says that the projector coefficients
+// of Xk are already in the workspace, and `project_next` leaves those of T
+// there for the next step of a filter.
 int hx_step(chfsi_op* op, int prec, const void* Xk, int64_t ldx, const void* Xp, int64_t ldp, void* T,
-            int64_t ldt, int64_t ncols, double alpha, double c, double beta, bool zero_prev) {
+            int64_t ldt, int64_t ncols, double alpha, double c, double beta, bool zero_prev, bool projected = false,
+            bool project_next = false) {
   chfsi_ctx* ctx = op->ctx;
   const HostTables& t = op->t;
   const bool single = is_single(prec);
@@ -256,10 +331,9 @@ int hx_step(chfsi_op* op, int prec, const void* Xk, int64_t ldx, const void* Xp,
     void* part = nullptr;
     CHECK(ws_get(ctx, WS_NLPART, static_cast<size_t>(op->nchunks) * 4 * ldhp * eb, &part));
     CHECK(ws_get(ctx, WS_HP, static_cast<size_t>(t.natoms) * 4 * ldhp * eb, &hP));
-    CHECK(nl_project(op, prec, Xk, ldx, ncols, part, hP, ldhp));
+    if (!projected) CHECK(nl_project(op, prec, Xk, ldx, ncols, part, hP, ldhp));
   }
-  HxLaunch L = make_hx(op, prec, Xk, ldx, Xp, ldp, T, ldt, ncols, alpha, c, beta, zero_prev, hP, ldhp);
-  const int kp = prec;
+  const bool tensor = tensor_path(op, prec, std::max({ldx, ldp, ldt}));
   if (ctx->deterministic) CHECK(build_colours(op));
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (ctx->timing) {
@@ -267,11 +341,22 @@ int hx_step(chfsi_op* op, int prec, const void* Xk, int64_t ldx, const void* Xp,
     HIP_TRY(ctx, hipEventCreate(&e1));
     HIP_TRY(ctx, hipEventRecord(e0, ctx->stream));
   }
-  CHECK(launch_hx_cells(op, L, kp));
+  if (tensor)
+    HIP_TRY(ctx, launch_tensor_hx(make_tensor(op, prec, Xk, ldx, Xp, ldp, T, ldt, ncols, alpha, c, beta), prec,
+                                  ctx->stream));
+  else
+    CHECK(launch_hx_cells(op, make_hx(op, prec, Xk, ldx, Xp, ldp, T, ldt, ncols, alpha, c, beta, zero_prev, hP, ldhp),
+                          prec));
   if (ctx->timing) {
     HIP_TRY(ctx, hipEventRecord(e1, ctx->stream));
     ctx->pending.emplace_back(e0, e1);
     ctx->pending_flops.push_back(cell_kernel_flops(op, ncols));
+  }
+  if (tensor && t.has_proj) {
+    void* pp = nullptr;
+    if (project_next)
+      CHECK(ws_get(ctx, WS_NLPAIR, static_cast<size_t>(op->nown_pairs) * 4 * ldhp * (single ? 4 : 8), &pp));
+    HIP_TRY(ctx, launch_nl_update(make_update(op, prec, T, ldt, ncols, alpha, hP, ldhp, pp), t.p, prec, ctx->stream));
   }
   return 0;
 }
@@ -309,6 +394,18 @@ int filter_block(chfsi_op* op, int prec, void* const R[4], int64_t ncols, const 
   std::vector<double> al, be;
   cheb_coeffs(m, a, b, aL, &c, al, be);
   const int sp = storage_of(prec);
+  if (tensor_path(op, prec, std::max(ldr[0], ldr[1]))) {
+    // two buffers: step i stores over X_{i - 2}, in place
+    CHECK(hx_step(op, prec, R[0], ldr[0], nullptr, ldr[0], R[1], ldr[1], ncols, al[0], c, 0.0, false, false,
+                  m > 1));
+    for (int i = 2; i <= m; ++i) {
+      const int k = (i - 1) % 2, t = i % 2;
+      CHECK(hx_step(op, prec, R[k], ldr[k], R[t], ldr[t], R[t], ldr[t], ncols, al[i - 1], c, be[i - 1], false,
+                    true, i < m));
+    }
+    *out_idx = m % 2;
+    return 0;
+  }
   for (int i = 1; i < 4; ++i) HIP_TRY(ctx, launch_fill(R[i], M, ncols * cf, ldr[i] * cf, sp, ctx->stream));
   CHECK(hx_step(op, prec, R[0], ldr[0], nullptr, ldr[0], R[1], ldr[1], ncols, al[0], c, 0.0, false));
   for (int i = 2; i <= m; ++i) {
@@ -331,13 +428,15 @@ int do_filter(chfsi_op* op, void* X, int64_t ncols, int64_t ld, int m, double a,
   // the work buffers' rows are padded to a multiple of 4 columns (16-byte
   // aligned rows for the bf16 kernel's block loads)
   const int64_t ldmax = (block + 3) / 4 * 4;
-  void* R[4];
-  for (int i = 0; i < 4; ++i) CHECK(ws_get(ctx, WS_R0 + i, static_cast<size_t>(t.M) * ldmax * eb, &R[i]));
+  const bool in_place = sp == xprec;
+  const bool tensor = tensor_path(op, prec, in_place ? std::max(ld, ldmax) : ldmax);
+  void* R[4] = {nullptr, nullptr, nullptr, nullptr};
+  for (int i = in_place ? 1 : 0; i < (tensor ? 2 : 4); ++i)
+    CHECK(ws_get(ctx, WS_R0 + i, static_cast<size_t>(t.M) * ldmax * eb, &R[i]));
   // in the block's own storage type the caller's block itself is the first
   // buffer of the rotation (no copy in; the owners clear its rows at step 2
   // for reuse as a target, and the result, unless it lands there, is copied
   // back over it)
-  const bool in_place = sp == xprec;
   for (int64_t c0 = 0; c0 < ncols; c0 += block) {
     const int64_t nb = std::min<int64_t>(block, ncols - c0);
     const int64_t ldw = (nb + 3) / 4 * 4;
@@ -473,7 +572,7 @@ int rayleigh_ritz(chfsi_op* op, const double* X, int64_t ldx, double* Psi, int64
   const int prec = cplx ? CHFSI_C128 : CHFSI_F64;
   void *W, *HPsi;
   CHECK(ws_get(ctx, WS_W, static_cast<size_t>(t.M) * N * 8 * cf, &W));
-  HIP_TRY(ctx, launch_fill(W, t.M, N * cf, N * cf, prec, ctx->stream));
+  if (!tensor_path(op, prec, std::max(ldx, N))) HIP_TRY(ctx, launch_fill(W, t.M, N * cf, N * cf, prec, ctx->stream));
   CHECK(hx_step(op, prec, X, ldx, nullptr, 0, W, N, N, 1.0, 0.0, 0.0, false));
   double* Hh = nullptr;
   CHECK(gram(op, X, ldx, static_cast<double*>(W), N, N, &Hh));
@@ -594,7 +693,7 @@ int rrgep_split(chfsi_op* op, double* X, int64_t ldx, int64_t N, int nfr, bool m
     return 0;
   };
   // RRGEP-P needs W = H~ X
-  HIP_TRY(ctx, launch_fill(W, M, nr, nr, prec, st));
+  if (!tensor_path(op, prec, std::max(ldx, N))) HIP_TRY(ctx, launch_fill(W, M, nr, nr, prec, st));
   CHECK(hx_step(op, prec, X, ldx, nullptr, 0, W, N, N, 1.0, 0.0, 0.0, false));
   float *X32 = nullptr, *W32 = nullptr;
   if (mixed) {
@@ -776,7 +875,8 @@ int do_bounds(chfsi_op* op, int steps, const double* v0_dev, const double* v0_ho
   HIP_TRY(ctx, launch_axpby(0.0, v, 1.0 / std::sqrt(nv), v, nr, ctx->stream));
   std::vector<double> al, be;
   // f = H v ; alpha = v.f ; f -= alpha v
-  HIP_TRY(ctx, launch_fill(f, t.M, cf, cf, prec, ctx->stream));
+  const bool tensor = tensor_path(op, prec, 1);
+  if (!tensor) HIP_TRY(ctx, launch_fill(f, t.M, cf, cf, prec, ctx->stream));
   CHECK(hx_step(op, prec, v, 1, nullptr, 1, f, 1, 1, 1.0, 0.0, 0.0, false));
   double alpha;
   CHECK(dot_host(ctx, v, f, nr, &alpha));
@@ -790,7 +890,7 @@ int do_bounds(chfsi_op* op, int steps, const double* v0_dev, const double* v0_ho
     // vprev <- v ; v <- f / beta ; f <- H v - beta vprev ; alpha ; f -= alpha v
     std::swap(v, vprev);
     HIP_TRY(ctx, launch_axpby(1.0 / beta, f, 0.0, v, nr, ctx->stream));
-    HIP_TRY(ctx, launch_fill(f, t.M, cf, cf, prec, ctx->stream));
+    if (!tensor) HIP_TRY(ctx, launch_fill(f, t.M, cf, cf, prec, ctx->stream));
     CHECK(hx_step(op, prec, v, 1, nullptr, 1, f, 1, 1, 1.0, 0.0, 0.0, false));
     HIP_TRY(ctx, launch_axpby(-beta, vprev, 1.0, f, nr, ctx->stream));
     CHECK(dot_host(ctx, v, f, nr, &alpha));
@@ -1485,6 +1585,11 @@ int chfsi_op_build(chfsi_ctx* ctx, const chfsi_system* sys, chfsi_op** out) {
       op->Ai64 = d;
       if ((rc = upload_f32(op.get(), sw, &op->Ai32)) < 0) break;
     }
+    std::vector<double> ts(kTensorTab);
+    pack_tensor_tables(t.p, t.ts_K.data(), t.ts_S.data(), t.ts_m.data(), ts.data());
+    if ((rc = upload(op.get(), ts, &d)) < 0) break;
+    op->ts_tab64 = d;
+    if ((rc = upload_f32(op.get(), ts, &op->ts_tab32)) < 0) break;
     if ((rc = upload(op.get(), t.vdiag, &op->vdiag)) < 0) break;
     if ((rc = upload(op.get(), t.dscale, &op->dscale)) < 0) break;
     if (t.has_proj) {
@@ -1506,6 +1611,16 @@ int chfsi_op_build(chfsi_ctx* ctx, const chfsi_system* sys, chfsi_op** out) {
       if ((rc = upload(op.get(), ca, &op->chunk_atom)) < 0) break;
       if ((rc = upload(op.get(), cb, &op->chunk_begin)) < 0) break;
       if ((rc = upload(op.get(), acp, &op->atom_chunk_ptr)) < 0) break;
+      if ((rc = upload(op.get(), t.own_cell, &op->own_cell)) < 0) break;
+      if ((rc = upload(op.get(), t.own_ptr, &op->own_ptr)) < 0) break;
+      if ((rc = upload(op.get(), t.own_atom, &op->own_atom)) < 0) break;
+      if ((rc = upload(op.get(), t.atom_pair_ptr, &op->atom_pair_ptr)) < 0) break;
+      if ((rc = upload(op.get(), t.atom_pair, &op->atom_pair)) < 0) break;
+      if ((rc = upload(op.get(), t.own_val, &d)) < 0) break;
+      op->own_val64 = d;
+      if ((rc = upload_f32(op.get(), t.own_val, &op->own_val32)) < 0) break;
+      op->nown_cells = static_cast<int>(t.own_cell.size());
+      op->nown_pairs = static_cast<int>(t.own_atom.size());
       if ((rc = upload(op.get(), t.pair_ptr, &op->pair_ptr)) < 0) break;
       if ((rc = upload(op.get(), t.pair_atom, &op->pair_atom)) < 0) break;
       op->npairs = static_cast<int64_t>(t.pair_atom.size());
@@ -1528,6 +1643,7 @@ int chfsi_op_build(chfsi_ctx* ctx, const chfsi_system* sys, chfsi_op** out) {
   std::vector<int32_t>().swap(t.atom_node);
   std::vector<double>().swap(t.pair_re);
   std::vector<double>().swap(t.pair_im);
+  std::vector<double>().swap(t.own_val);
   // deterministic assembly already on: the colour classes now, so that no
   // later call has to allocate them (operators with one cell per side have
   // none and are refused at their first H~.X)
@@ -1736,7 +1852,7 @@ int chfsi_apply(chfsi_op* op, const void* X, void* Y, int64_t ncols, int64_t ld,
   if (X == Y) return fail(ctx, CHFSI_EINVAL, "X and Y must not overlap");
   const int cf = op->t.cplx ? 2 : 1;
   const int sp = storage_of(prec);
-  HIP_TRY(ctx, launch_fill(Y, op->t.M, ncols * cf, ld * cf, sp, ctx->stream));
+  if (!tensor_path(op, prec, ld)) HIP_TRY(ctx, launch_fill(Y, op->t.M, ncols * cf, ld * cf, sp, ctx->stream));
   return hx_step(op, prec, X, ld, nullptr, ld, Y, ld, ncols, 1.0, 0.0, 0.0, false);
 }
 
@@ -1761,12 +1877,21 @@ int chfsi_apply_noalloc(chfsi_op* op, const void* X, void* Y, int64_t ncols, int
                     std::to_string(ncols) + " columns; the fixed scratch holds " + std::to_string(kScratchBytes) +
                     " (use fewer columns per call, or chfsi_apply)");
   if (t.has_proj && !ctx->scratch) return fail(ctx, CHFSI_EHIP, "fixed scratch unavailable: " + ctx->scratch_err);
-  HIP_TRY(ctx, launch_fill(Y, t.M, ncols * cf, ld * cf, sp, ctx->stream));
+  const bool tensor = tensor_path(op, prec, ld);
+  if (!tensor) HIP_TRY(ctx, launch_fill(Y, t.M, ncols * cf, ld * cf, sp, ctx->stream));
   void* hP = nullptr;
   if (t.has_proj) {
     char* base = static_cast<char*>(ctx->scratch);
     hP = base + part_bytes;
     CHECK(nl_project(op, prec, X, ld, ncols, base, hP, ldhp));
+  }
+  if (tensor) {
+    CHECK(deterministic_ready(op));
+    HIP_TRY(ctx, launch_tensor_hx(make_tensor(op, prec, X, ld, nullptr, ld, Y, ld, ncols, 1.0, 0.0, 0.0), prec,
+                                  ctx->stream));
+    if (t.has_proj)
+      HIP_TRY(ctx, launch_nl_update(make_update(op, prec, Y, ld, ncols, 1.0, hP, ldhp, nullptr), t.p, prec, ctx->stream));
+    return 0;
   }
   const HxLaunch L = make_hx(op, prec, X, ld, nullptr, ld, Y, ld, ncols, 1.0, 0.0, 0.0, false, hP, ldhp);
   return launch_hx_cells(op, L, prec);

@@ -16,6 +16,7 @@ namespace chfsi_host {
 enum Slot {
   WS_R0, WS_R1, WS_R2, WS_R3,      // filter buffers
   WS_NLPART, WS_HP,                // projector partials / scaled coefficients
+  WS_NLPAIR,                       // partial projections per (cell, atom) pair
   WS_GPART, WS_G, WS_S, WS_Z, WS_Z2,
   WS_W, WS_X2, WS_HPSI,            // M x N work blocks
   WS_RPART, WS_VEC, WS_SMALL, WS_EIG, WS_INFO,
@@ -98,6 +99,15 @@ struct chfsi_op {
   int32_t* pair_atom = nullptr;
   void* pair_re64 = nullptr; void* pair_im64 = nullptr;
   void* pair_re32 = nullptr; void* pair_im32 = nullptr;
+  void* ts_tab64 = nullptr; void* ts_tab32 = nullptr;   // 1D factors of the cell matrix (tensor-product path)
+  // owned-node projector tables (nonlocal update)
+  int32_t* own_cell = nullptr;
+  int32_t* own_ptr = nullptr;
+  int32_t* own_atom = nullptr;
+  int32_t* atom_pair_ptr = nullptr;
+  int32_t* atom_pair = nullptr;
+  void* own_val64 = nullptr; void* own_val32 = nullptr;
+  int nown_cells = 0, nown_pairs = 0;
   double* d_x1d = nullptr;      // node coordinates along one axis (features)
   double* d_atoms = nullptr;    // atom table (features)
   // colour classes of the cells for deterministic assembly: the cells of

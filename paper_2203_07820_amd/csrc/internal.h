@@ -49,6 +49,16 @@ struct HostTables {
   std::vector<int32_t> pair_atom;   // npairs
   std::vector<double> pair_re;      // npairs * (mpad/16) * 64
   std::vector<double> pair_im;      // complex only
+  // 1D factors of the cell matrix, (p+1) x (p+1), Loewdin-scaled and
+  // independent of h: half the stiffness, skew derivative; m with
+  // diag(1/2, 1, .., 1, 1/2) - m m^T the mass
+  std::vector<double> ts_K, ts_S, ts_m;
+  // (owner cell, atom) pairs sorted by cell, with the projector values of the
+  // cell's p^3 owned nodes (local indices < p), [pair][z][y][x][4 (x2)]: the
+  // cells that have pairs, their pairs, and the pairs of every atom
+  std::vector<int32_t> own_cell, own_ptr, own_atom;
+  std::vector<double> own_val;
+  std::vector<int32_t> atom_pair_ptr, atom_pair;
   std::vector<double> atoms;        // natoms x 8: x, y, z, Z, s, h_s, h_p, 0
 };
 
@@ -99,6 +109,28 @@ struct HxLaunch {
 // prec: CHFSI_F64 / F32 / BF16 (real), C128 / C64 (complex, data real view).
 hipError_t launch_cell_hx(const HxLaunch& a, int prec, hipStream_t s);
 
+// H~.X without its nonlocal term through the tensor-product form of the cell
+// matrix (kernels_tensor.hip), for operators whose cells share one cell
+// matrix: T = alpha (H~ Xk - c Xk) - beta Xp, every entry of T written once; T
+// may be Xp.  prec: CHFSI_F64 / F32 / C128 / C64 (real view).
+struct TensorLaunch {
+  int p, nc;                       // order, cells per side
+  int ncols;                       // real columns
+  int ncu;                         // compute units
+  double h;                        // cell side
+  double kh[3];                    // k_d h
+  const void* tab;                 // device: packed 1D factors (pack_tensor_tables), in the kernel's real type
+  const double* vdiag;
+  const void* Xk; int64_t ldx;     // real view
+  const void* Xp; int64_t ldp;     // nullable
+  void* T; int64_t ldt;
+  double alpha, c, beta;
+};
+// The 1D factors (HostTables ts_K, ts_S, ts_m) as the kernel reads them.
+constexpr int kTensorTab = 68 + 8 * 24;
+void pack_tensor_tables(int p, const double* K1, const double* S1, const double* m1, double* out);
+hipError_t launch_tensor_hx(const TensorLaunch& L, int prec, hipStream_t s);
+
 // Many problems of the same order and precision in one persistent launch.
 // descs: device array of nprob packed kernel argument blocks (pack_hx_desc);
 // item_off: device array of nprob + 1 item offsets (items of problem q are
@@ -145,6 +177,23 @@ struct NlBatch {
   int max_col_tiles, max_row_blocks;
 };
 hipError_t launch_nl_project_batched(const NlBatch& b, int prec, hipStream_t s);
+
+// Y += alpha C (h P) on the nodes the projectors touch, and (part not null)
+// h P <- h C^H Y of the updated block.
+struct NlUpdate {
+  int natoms, ncells, nc;           // cells that own touched nodes
+  int ncols, nreal;                 // logical and real columns
+  const int32_t* cells; const int32_t* pair_ptr; const int32_t* pair_atom;
+  const void* val;                  // [pair][p^3][4 (x2)]
+  const int32_t* atom_pair_ptr; const int32_t* atom_pair;
+  const double* hcoef;
+  void* Y; int64_t ldy;             // logical ld
+  double alpha;
+  int update;                       // 0: projection only
+  void* hP; int64_t ldhp;           // real view
+  void* part;                       // pairs x 4 x ldhp (real view), or null
+};
+hipError_t launch_nl_update(const NlUpdate& a, int p, int prec, hipStream_t s);
 
 // Size of the fixed device scratch of chfsi_apply_noalloc() (kernels_nl.hip),
 // and its device address on the current device (call with that device

@@ -169,6 +169,170 @@ hipError_t nl_launch(const NlLaunch& L, hipStream_t s) {
   return hipGetLastError();
 }
 
+// ---- nonlocal update fused with the next projection -----------------------------
+// Y += alpha C (h P) on the nodes that the projectors touch, and, from the
+// updated values while they are in registers, the partial projections
+// C^H Y of the next step (Algorithm 4 steps 1-6 around one Chebyshev step).
+// The tensor-product kernel leaves the nonlocal term out: its waves have no
+// registers left for it (in it, with the projector values as A operands of
+// one MFMA per (cell, atom) pair, the term cost 0.6-0.9 ms of a 128-column
+// FP64 step on the 24^3-cell p = 6 operator; reading and writing the touched
+// rows here costs about what reading them for the projection alone did).
+// One workgroup of 8 waves per (cell that owns touched nodes, 64 columns).  A
+// wave holds its share of the cell's p^3 owned rows in registers (all loads
+// in flight together); the projector values are uniform over a wave (scalar
+// loads).  Partial projections of a (cell, atom) pair are summed over the
+// waves in a fixed order and stored; nl_pair_reduce_kernel sums them per atom.
+template <typename T> using cptr = const __attribute__((address_space(4))) T*;
+
+template <int P, typename T, bool CPLX>
+__device__ __forceinline__ void nl_update_item(const NlUpdate& a, const int item, const int ctile) {
+  constexpr int P3 = P * P * P, NW = 8, NPW = (P3 + NW - 1) / NW, CF = CPLX ? 2 : 1;
+  __shared__ T red[NW][4 * CF][64];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+  const int lane = threadIdx.x % 64;
+  const int col = ctile * 64 + lane;   // logical column
+  const bool ok = col < a.ncols;
+  const int colc = ok ? col : a.ncols - 1;
+  const int cell = a.cells[item];
+  const int p0 = a.pair_ptr[item], p1 = a.pair_ptr[item + 1];
+  const int nc = a.nc, n = nc * P;
+  const int64_t base = static_cast<int64_t>(cell % nc) * P +
+                       static_cast<int64_t>(n) * ((cell / nc) % nc * P + static_cast<int64_t>(n) * (cell / (nc * nc) * P));
+  const gptr<T> Y = to_global(static_cast<T*>(a.Y)) + static_cast<int64_t>(colc) * CF;
+  const int i0 = wave * NPW;
+  // row of owned node i (past the end: the last one, not used)
+  auto row = [&](int i) {
+    const int e = i0 + i < P3 ? i0 + i : P3 - 1;
+    return (base + e % P + static_cast<int64_t>(n) * (e / P % P + static_cast<int64_t>(n) * (e / (P * P)))) * a.ldy * CF;
+  };
+  T yr[NPW], yi[CPLX ? NPW : 1];
+#pragma unroll
+  for (int i = 0; i < NPW; ++i) {
+    const int64_t r = row(i);
+    yr[i] = Y[r];
+    if constexpr (CPLX) yi[i] = Y[r + 1];
+  }
+  const cptr<T> val = (cptr<T>)static_cast<const T*>(a.val);
+  if (a.update) {
+    const T al = static_cast<T>(a.alpha);
+    for (int pr = p0; pr < p1; ++pr) {
+      const gptr<const T> h = to_global(static_cast<const T*>(a.hP)) +
+                              static_cast<int64_t>(a.pair_atom[pr]) * 4 * a.ldhp + static_cast<int64_t>(colc) * CF;
+      T hr[4], hi[CPLX ? 4 : 1];
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        hr[m] = al * h[m * a.ldhp];
+        if constexpr (CPLX) hi[m] = al * h[m * a.ldhp + 1];
+      }
+#pragma unroll
+      for (int i = 0; i < NPW; ++i) {
+        if (P3 % NW != 0 && i0 + i >= P3) continue;
+        const cptr<T> v = val + (static_cast<int64_t>(pr) * P3 + i0 + i) * 4 * CF;
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+          if constexpr (CPLX) {
+            yr[i] += v[2 * m] * hr[m];
+            yr[i] -= v[2 * m + 1] * hi[m];
+            yi[i] += v[2 * m] * hi[m];
+            yi[i] += v[2 * m + 1] * hr[m];
+          } else {
+            yr[i] += v[m] * hr[m];
+          }
+        }
+      }
+    }
+    if (ok) {
+#pragma unroll
+      for (int i = 0; i < NPW; ++i) {
+        if (P3 % NW != 0 && i0 + i >= P3) continue;
+        const int64_t r = row(i);
+        Y[r] = yr[i];
+        if constexpr (CPLX) Y[r + 1] = yi[i];
+      }
+    }
+  }
+  if (!a.part) return;
+  const gptr<T> part = to_global(static_cast<T*>(a.part));
+  for (int pr = p0; pr < p1; ++pr) {
+    T acc[4 * CF];
+#pragma unroll
+    for (int m = 0; m < 4 * CF; ++m) acc[m] = T(0);
+#pragma unroll
+    for (int i = 0; i < NPW; ++i) {
+      if (P3 % NW != 0 && i0 + i >= P3) continue;
+      const cptr<T> v = val + (static_cast<int64_t>(pr) * P3 + i0 + i) * 4 * CF;
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        if constexpr (CPLX) {   // conj(c) y
+          acc[2 * m] += v[2 * m] * yr[i];
+          acc[2 * m] += v[2 * m + 1] * yi[i];
+          acc[2 * m + 1] += v[2 * m] * yi[i];
+          acc[2 * m + 1] -= v[2 * m + 1] * yr[i];
+        } else {
+          acc[m] += v[m] * yr[i];
+        }
+      }
+    }
+    __syncthreads();   // the previous pair's sums are read
+#pragma unroll
+    for (int m = 0; m < 4 * CF; ++m) red[wave][m][lane] = acc[m];
+    __syncthreads();
+    for (int m = wave; m < 4 * CF; m += NW) {
+      T s = red[0][m][lane];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) s += red[w][m][lane];
+      if (ok) part[(static_cast<int64_t>(pr) * 4 + m / CF) * a.ldhp + static_cast<int64_t>(col) * CF + m % CF] = s;
+    }
+  }
+}
+
+template <int P, typename T, bool CPLX>
+__global__ void __launch_bounds__(512) nl_update_kernel(const NlUpdate a) {
+  nl_update_item<P, T, CPLX>(a, blockIdx.x, blockIdx.y);
+}
+
+// hP[atom][m] = h sum over the atom's pairs of their partial projections
+template <typename T>
+__device__ __forceinline__ void nl_pair_reduce_item(const NlUpdate& a, const int am, const int jblk) {
+  const int at = am / 4, m = am % 4;
+  const int j = jblk * 256 + threadIdx.x;
+  if (j >= a.ldhp) return;
+  T s = T(0);
+  if (j < a.nreal) {
+    const gptr<const T> part = to_global(static_cast<const T*>(a.part)) + j + m * a.ldhp;
+    const int e1 = a.atom_pair_ptr[at + 1];
+#pragma unroll 8
+    for (int e = a.atom_pair_ptr[at]; e < e1; ++e) s += part[static_cast<int64_t>(a.atom_pair[e]) * 4 * a.ldhp];
+    s *= static_cast<T>(a.hcoef[am]);
+  }
+  to_global(static_cast<T*>(a.hP))[static_cast<int64_t>(am) * a.ldhp + j] = s;
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256) nl_pair_reduce_kernel(const NlUpdate a) {
+  nl_pair_reduce_item<T>(a, blockIdx.x, blockIdx.y);
+}
+
+template <typename T, bool CPLX>
+hipError_t nl_update_launch(const NlUpdate& a, int p, hipStream_t s) {
+  const dim3 g(a.ncells, (a.ncols + 63) / 64);
+  if (a.ncells > 0) {
+    switch (p) {
+      case 2: hipLaunchKernelGGL((nl_update_kernel<2, T, CPLX>), g, dim3(512), 0, s, a); break;
+      case 3: hipLaunchKernelGGL((nl_update_kernel<3, T, CPLX>), g, dim3(512), 0, s, a); break;
+      case 4: hipLaunchKernelGGL((nl_update_kernel<4, T, CPLX>), g, dim3(512), 0, s, a); break;
+      case 5: hipLaunchKernelGGL((nl_update_kernel<5, T, CPLX>), g, dim3(512), 0, s, a); break;
+      case 6: hipLaunchKernelGGL((nl_update_kernel<6, T, CPLX>), g, dim3(512), 0, s, a); break;
+      case 7: hipLaunchKernelGGL((nl_update_kernel<7, T, CPLX>), g, dim3(512), 0, s, a); break;
+      default: return hipErrorInvalidValue;
+    }
+  }
+  if (a.part)
+    hipLaunchKernelGGL((nl_pair_reduce_kernel<T>), dim3(a.natoms * 4, (a.ldhp + 255) / 256), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
 // ---- elementwise helpers ----------------------------------------------------
 template <typename T>
 __global__ void fill_kernel(T* dst, int64_t rows, int64_t cols, int64_t ld) {
@@ -219,6 +383,16 @@ hipError_t launch_nl_project(const NlLaunch& L, int prec, hipStream_t s) {
     case CHFSI_BF16: return nl_launch<float, false>(L, s);
     case CHFSI_C128: return nl_launch<double, true>(L, s);
     case CHFSI_C64: return nl_launch<float, true>(L, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+hipError_t launch_nl_update(const NlUpdate& a, int p, int prec, hipStream_t s) {
+  switch (prec) {
+    case CHFSI_F64: return nl_update_launch<double, false>(a, p, s);
+    case CHFSI_F32: return nl_update_launch<float, false>(a, p, s);
+    case CHFSI_C128: return nl_update_launch<double, true>(a, p, s);
+    case CHFSI_C64: return nl_update_launch<float, true>(a, p, s);
     default: return hipErrorInvalidValue;
   }
 }

@@ -197,6 +197,26 @@ std::string build_tables(const chfsi_system& sys, HostTables& t) {
   }
   for (int i = 0; i < p; ++i) dd_glob[i] = dd_loc[i];
 
+  // the scaled 1D factors: D_c is a product of dd_loc, and d_a d_b times h^2
+  // (stiffness) or h (derivative) does not depend on h.  The GLL rule is exact
+  // for products of degree < 2p and gives 2/p instead of 2/(2p + 1) for the
+  // norm of P_p, so Mc = (h/2) (diag(w) - g (w l)(w l)^T) with l_a = P_p(x_a),
+  // g = (2/p - 2/(2p + 1)) / (2/p)^2: scaled, diag(1/2, 1, .., 1, 1/2) - m m^T
+  t.ts_K.resize(q * q);
+  t.ts_S.resize(q * q);
+  t.ts_m.resize(q);
+  for (int a = 0; a < q; ++a) {
+    for (int b = 0; b < q; ++b) {
+      const double dd = dd_loc[a] * dd_loc[b];
+      t.ts_K[a * q + b] = 0.5 * dd * K1[a * q + b] * h * h;
+      t.ts_S[a * q + b] = 0.5 * dd * (G1[a * q + b] - G1[b * q + a]) * h;
+    }
+    double P = (a == p || p % 2 == 0) ? 1.0 : -1.0, dP;   // P_p(+-1)
+    if (a > 0 && a < p) legendre_pd(p, xi[a], P, dP);
+    const double g = (2.0 / p - 2.0 / (2.0 * p + 1.0)) * p * p / 4.0;
+    t.ts_m[a] = std::sqrt(g * wl[a] * (a == 0 || a == p ? 0.5 : 1.0)) * P;
+  }
+
   // ---- reference cell matrix A_k = D_c (K^c/2 - i skew(k.G^c)/2) D_c
   const int mc = t.mcell;
   t.cell_re.assign(static_cast<size_t>(mc) * mc, 0.0);
@@ -292,12 +312,21 @@ std::string build_tables(const chfsi_system& sys, HostTables& t) {
   t.pair_re.clear();
   t.pair_im.clear();
   t.hcoef.assign(4 * sys.natoms, 0.0);
+  t.own_cell.clear();
+  t.own_ptr.clear();
+  t.own_atom.clear();
+  t.own_val.clear();
+  t.atom_pair_ptr.assign(1, 0);
+  t.atom_pair.clear();
   if (!t.has_proj) return "";
   const int vw = t.cplx ? 8 : 4;
   using cd = std::complex<double>;
   struct Entry { int64_t node; cd v[4]; };
   struct PairRec { int64_t cell; int atom; std::vector<double> cre, cim; };
   std::vector<PairRec> pairs;
+  struct OwnRec { int64_t cell; int atom; std::vector<double> v; };
+  std::vector<OwnRec> owns;
+  const size_t p3 = static_cast<size_t>(p) * p * p;
   std::vector<Entry> ent;
   for (int at = 0; at < sys.natoms; ++at) {
     const double w = sys.w[at];
@@ -342,7 +371,7 @@ std::string build_tables(const chfsi_system& sys, HostTables& t) {
         }
     std::sort(ent.begin(), ent.end(), [](const Entry& a, const Entry& b) { return a.node < b.node; });
     // merge overlapping images, append to the atom-major list
-    std::unordered_map<int64_t, size_t> cell_pair;
+    std::unordered_map<int64_t, size_t> cell_pair, cell_own;
     for (size_t i = 0; i < ent.size();) {
       Entry e = ent[i];
       size_t j = i + 1;
@@ -360,9 +389,24 @@ std::string build_tables(const chfsi_system& sys, HostTables& t) {
           t.atom_val.push_back(e.v[m].real());
         }
       }
-      // the cells holding this node, with its local index and multiplicity
       const int ix = static_cast<int>(e.node % n), iy = static_cast<int>((e.node / n) % n),
                 iz = static_cast<int>(e.node / (static_cast<int64_t>(n) * n));
+      // the owner cell's table
+      {
+        const int64_t cell = ix / p + static_cast<int64_t>(nc) * (iy / p + static_cast<int64_t>(nc) * (iz / p));
+        const auto ins = cell_own.emplace(cell, owns.size());
+        if (ins.second) owns.push_back(OwnRec{cell, at, std::vector<double>(p3 * vw, 0.0)});
+        double* o = &owns[ins.first->second].v[(ix % p + p * (iy % p + static_cast<size_t>(p) * (iz % p))) * vw];
+        for (int m = 0; m < 4; ++m) {
+          if (t.cplx) {
+            o[2 * m] = e.v[m].real();
+            o[2 * m + 1] = e.v[m].imag();
+          } else {
+            o[m] = e.v[m].real();
+          }
+        }
+      }
+      // the cells holding this node, with its local index and multiplicity
       int cxs[2], axs[2], ncx = 0, cys[2], ays[2], ncy = 0, czs[2], azs[2], ncz = 0;
       auto cells_of = [&](int i1, int* cs, int* as, int& cnt) {
         cnt = 0;
@@ -400,7 +444,30 @@ std::string build_tables(const chfsi_system& sys, HostTables& t) {
     }
     t.atom_ptr.push_back(static_cast<int64_t>(t.atom_node.size()));
   }
-  (void)vw;
+  // owner tables sorted by (cell, atom)
+  std::vector<size_t> oo(owns.size());
+  for (size_t i = 0; i < oo.size(); ++i) oo[i] = i;
+  std::sort(oo.begin(), oo.end(), [&](size_t a, size_t b) {
+    return owns[a].cell != owns[b].cell ? owns[a].cell < owns[b].cell : owns[a].atom < owns[b].atom;
+  });
+  t.own_atom.resize(owns.size());
+  t.own_val.resize(owns.size() * p3 * vw);
+  std::vector<std::vector<int32_t>> of_atom(sys.natoms);
+  for (size_t i = 0; i < oo.size(); ++i) {
+    const OwnRec& o = owns[oo[i]];
+    if (t.own_cell.empty() || t.own_cell.back() != o.cell) {
+      t.own_cell.push_back(static_cast<int32_t>(o.cell));
+      t.own_ptr.push_back(static_cast<int32_t>(i));
+    }
+    t.own_atom[i] = o.atom;
+    of_atom[o.atom].push_back(static_cast<int32_t>(i));
+    std::copy(o.v.begin(), o.v.end(), t.own_val.begin() + i * p3 * vw);
+  }
+  t.own_ptr.push_back(static_cast<int32_t>(oo.size()));
+  for (int at = 0; at < sys.natoms; ++at) {
+    t.atom_pair.insert(t.atom_pair.end(), of_atom[at].begin(), of_atom[at].end());
+    t.atom_pair_ptr.push_back(static_cast<int32_t>(t.atom_pair.size()));
+  }
   // pairs sorted by (cell, atom), cell-major CSR, MFMA A-operand layout:
   // lane -> (row lane%16 of the row tile, projector component lane/16)
   std::vector<size_t> ord(pairs.size());
