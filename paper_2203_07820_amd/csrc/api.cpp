@@ -304,7 +304,6 @@ NlUpdate make_update(const chfsi_op* op, int prec, void* Y, int64_t ldy, int64_t
   u.Y = Y;
   u.ldy = ldy;
   u.alpha = alpha;
-  u.update = 1;
   u.hP = hP;
   u.ldhp = ldhp;
   u.part = part;

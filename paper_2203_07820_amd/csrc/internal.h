@@ -54,8 +54,9 @@ struct HostTables {
   // diag(1/2, 1, .., 1, 1/2) - m m^T the mass
   std::vector<double> ts_K, ts_S, ts_m;
   // (owner cell, atom) pairs sorted by cell, with the projector values of the
-  // cell's p^3 owned nodes (local indices < p), [pair][z][y][x][4 (x2)]: the
-  // cells that have pairs, their pairs, and the pairs of every atom
+  // cell's p^3 owned nodes (local indices < p, x fastest) in tiles of 16,
+  // [pair][tile][re, im][projector][node]: the cells that have pairs, their
+  // pairs, and the pairs of every atom
   std::vector<int32_t> own_cell, own_ptr, own_atom;
   std::vector<double> own_val;
   std::vector<int32_t> atom_pair_ptr, atom_pair;
@@ -184,12 +185,11 @@ struct NlUpdate {
   int natoms, ncells, nc;           // cells that own touched nodes
   int ncols, nreal;                 // logical and real columns
   const int32_t* cells; const int32_t* pair_ptr; const int32_t* pair_atom;
-  const void* val;                  // [pair][p^3][4 (x2)]
+  const void* val;                  // HostTables own_val
   const int32_t* atom_pair_ptr; const int32_t* atom_pair;
   const double* hcoef;
   void* Y; int64_t ldy;             // logical ld
   double alpha;
-  int update;                       // 0: projection only
   void* hP; int64_t ldhp;           // real view
   void* part;                       // pairs x 4 x ldhp (real view), or null
 };

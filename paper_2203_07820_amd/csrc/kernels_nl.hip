@@ -4,6 +4,8 @@
 // helpers of the filter (zero fill, precision conversion of a block).
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "device_util.h"
 #include "internal.h"
 
@@ -174,162 +176,257 @@ hipError_t nl_launch(const NlLaunch& L, hipStream_t s) {
 // updated values while they are in registers, the partial projections
 // C^H Y of the next step (Algorithm 4 steps 1-6 around one Chebyshev step).
 // The tensor-product kernel leaves the nonlocal term out: its waves have no
-// registers left for it (in it, with the projector values as A operands of
-// one MFMA per (cell, atom) pair, the term cost 0.6-0.9 ms of a 128-column
-// FP64 step on the 24^3-cell p = 6 operator; reading and writing the touched
-// rows here costs about what reading them for the projection alone did).
-// One workgroup of 8 waves per (cell that owns touched nodes, 64 columns).  A
-// wave holds its share of the cell's p^3 owned rows in registers (all loads
-// in flight together); the projector values are uniform over a wave (scalar
-// loads).  Partial projections of a (cell, atom) pair are summed over the
-// waves in a fixed order and stored; nl_pair_reduce_kernel sums them per atom.
-template <typename T> using cptr = const __attribute__((address_space(4))) T*;
+// registers left for it, and reading and writing the touched rows here costs
+// little more than reading them for the projection alone.
+// Bound by memory: the touched rows are read and written once.  On the
+// 24^3-cell p = 6 operator with 64 atoms, 128 columns, FP64, most of a 3.06 GB
+// block and 1.06 ms per step; rows in registers of an 8-wave workgroup with the
+// projections on vector FMAs and a sum over the waves took 1.10 ms there, and
+// 0.21 against 0.16 ms on 12^3 cells, p = 5, 160 columns, where the chains of
+// dependent loads show.
+// One wave per (cell that owns touched nodes, 32 real columns): no barriers.
+// It walks over the cell's owned nodes in tiles of 16, the next tile's rows in
+// flight.  Both products run on the 16x16x4 MFMA: the accumulator layout of a
+// tile (16 nodes x 16 columns) is also the layout in which its values enter
+// the projection as an operand (16 columns x 4 nodes per step), and the
+// projectors of 4 atoms fill its other 16 rows.  Cells with more than 4 atoms
+// read their rows again for the further atoms' projections.  32 columns: with
+// 16 the projector values are read twice as often (3 % of a filter), with 64
+// two waves per SIMD fit instead of four (3 % on the 12^3 box).
+constexpr int kNlGroups = 2;   // groups of 16 real columns per wave
+typedef double nd4 __attribute__((ext_vector_type(4)));
+typedef float nf4 __attribute__((ext_vector_type(4)));
+template <typename T> struct NlMma;
+template <> struct NlMma<double> {
+  typedef nd4 acc;
+  static __device__ __forceinline__ acc run(double a, double b, acc c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+  // row of the accumulator's register i in lane group q
+  static __device__ __forceinline__ int row(int i, int q) { return 4 * i + q; }
+};
+template <> struct NlMma<float> {
+  typedef nf4 acc;
+  static __device__ __forceinline__ acc run(float a, float b, acc c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int i, int q) { return 4 * q + i; }
+};
+// (re, im) -> (im, -re) of interleaved columns, one real column per lane
+__device__ __forceinline__ int nl_swap(int v) { return __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true); }
+__device__ __forceinline__ double nl_rot(double v, int lane) {
+  const double o = __hiloint2double(nl_swap(__double2hiint(v)), nl_swap(__double2loint(v)));
+  return (lane & 1) ? -o : o;
+}
+__device__ __forceinline__ float nl_rot(float v, int lane) {
+  const float o = __int_as_float(nl_swap(__float_as_int(v)));
+  return (lane & 1) ? -o : o;
+}
 
 template <int P, typename T, bool CPLX>
-__device__ __forceinline__ void nl_update_item(const NlUpdate& a, const int item, const int ctile) {
-  constexpr int P3 = P * P * P, NW = 8, NPW = (P3 + NW - 1) / NW, CF = CPLX ? 2 : 1;
-  __shared__ T red[NW][4 * CF][64];
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
-  const int lane = threadIdx.x % 64;
-  const int col = ctile * 64 + lane;   // logical column
-  const bool ok = col < a.ncols;
-  const int colc = ok ? col : a.ncols - 1;
+__device__ __forceinline__ void nl_update_item(const NlUpdate& a, const int item, const int ctile,
+                                               const int32_t* noff) {
+    constexpr int P3 = P * P * P, NT = (P3 + 15) / 16, CV = CPLX ? 2 : 1, NC = kNlGroups;
+  typedef typename NlMma<T>::acc acc_t;
+  const int lane = threadIdx.x % 64, q = lane / 16, cl = lane % 16;
   const int cell = a.cells[item];
-  const int p0 = a.pair_ptr[item], p1 = a.pair_ptr[item + 1];
+  const int p0 = a.pair_ptr[item], np = a.pair_ptr[item + 1] - p0;
   const int nc = a.nc, n = nc * P;
   const int64_t base = static_cast<int64_t>(cell % nc) * P +
                        static_cast<int64_t>(n) * ((cell / nc) % nc * P + static_cast<int64_t>(n) * (cell / (nc * nc) * P));
-  const gptr<T> Y = to_global(static_cast<T*>(a.Y)) + static_cast<int64_t>(colc) * CF;
-  const int i0 = wave * NPW;
-  // row of owned node i (past the end: the last one, not used)
-  auto row = [&](int i) {
-    const int e = i0 + i < P3 ? i0 + i : P3 - 1;
-    return (base + e % P + static_cast<int64_t>(n) * (e / P % P + static_cast<int64_t>(n) * (e / (P * P)))) * a.ldy * CF;
-  };
-  T yr[NPW], yi[CPLX ? NPW : 1];
+  const int64_t ld = a.ldy * (CPLX ? 2 : 1);
+  const gptr<T> Y = to_global(static_cast<T*>(a.Y)) + base * ld;
+  int col[NC];
+  bool ok[NC];
 #pragma unroll
-  for (int i = 0; i < NPW; ++i) {
-    const int64_t r = row(i);
-    yr[i] = Y[r];
-    if constexpr (CPLX) yi[i] = Y[r + 1];
+  for (int c = 0; c < NC; ++c) {
+    col[c] = ctile * (16 * NC) + c * 16 + cl;
+    ok[c] = col[c] < a.nreal;
+    if (!ok[c]) col[c] = CPLX ? a.nreal - 2 + (cl & 1) : a.nreal - 1;
   }
-  const cptr<T> val = (cptr<T>)static_cast<const T*>(a.val);
-  if (a.update) {
-    const T al = static_cast<T>(a.alpha);
-    for (int pr = p0; pr < p1; ++pr) {
-      const gptr<const T> h = to_global(static_cast<const T*>(a.hP)) +
-                              static_cast<int64_t>(a.pair_atom[pr]) * 4 * a.ldhp + static_cast<int64_t>(colc) * CF;
-      T hr[4], hi[CPLX ? 4 : 1];
+  struct Tile {
+    int32_t off[4];   // nodes from the cell's first node
+    T y[NC][4];
+  };
+  auto load = [&](int t, Tile& u) {
 #pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        hr[m] = al * h[m * a.ldhp];
-        if constexpr (CPLX) hi[m] = al * h[m * a.ldhp + 1];
+    for (int i = 0; i < 4; ++i) {
+      u.off[i] = noff[t * 16 + NlMma<T>::row(i, q)];
+#pragma unroll
+      for (int c = 0; c < NC; ++c) u.y[c][i] = Y[u.off[i] * ld + col[c]];
+    }
+  };
+  const gptr<const T> val = to_global(static_cast<const T*>(a.val)) + static_cast<int64_t>(p0) * NT * CV * 64;
+  const gptr<const T> hp = to_global(static_cast<const T*>(a.hP));
+  const T al = static_cast<T>(a.alpha);
+  T hb[4][NC];   // alpha h P of the first four atoms, B operands
+  auto load_h = [&](int g, T (&h)[NC]) {
+    const gptr<const T> r = hp + (static_cast<int64_t>(a.pair_atom[p0 + g]) * 4 + q) * a.ldhp;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) h[c] = al * r[col[c]];
+  };
+#pragma unroll
+  for (int g = 0; g < 4; ++g)
+    if (g < np) load_h(g, hb[g]);
+  auto add = [&](int g, int t, const T (&h)[NC], Tile& u) {
+    T cv[CV];
+#pragma unroll
+    for (int v = 0; v < CV; ++v) cv[v] = val[((static_cast<int64_t>(g) * NT + t) * CV + v) * 64 + lane];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      acc_t d = {u.y[c][0], u.y[c][1], u.y[c][2], u.y[c][3]};
+      d = NlMma<T>::run(cv[0], h[c], d);
+      if constexpr (CPLX) d = NlMma<T>::run(cv[1], -nl_rot(h[c], lane), d);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) u.y[c][i] = d[i];
+    }
+  };
+  acc_t pj[NC];   // projections: 16 columns x 4 projectors of 4 atoms
+  auto clear = [&]() {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) pj[c] = acc_t{0, 0, 0, 0};
+  };
+  // projections of atoms g0 .. g0 + 3 from the rows of tile t
+  auto project = [&](int g0, int t, const Tile& u) {
+    const int g = g0 + cl / 4;
+    const bool in = g < np;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      T b[CV];
+#pragma unroll
+      for (int v = 0; v < CV; ++v) {
+        const T e = val[((static_cast<int64_t>(in ? g : 0) * NT + t) * CV + v) * 64 + cl % 4 * 16 + NlMma<T>::row(i, q)];
+        b[v] = in ? e : T(0);
       }
 #pragma unroll
-      for (int i = 0; i < NPW; ++i) {
-        if (P3 % NW != 0 && i0 + i >= P3) continue;
-        const cptr<T> v = val + (static_cast<int64_t>(pr) * P3 + i0 + i) * 4 * CF;
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-          if constexpr (CPLX) {
-            yr[i] += v[2 * m] * hr[m];
-            yr[i] -= v[2 * m + 1] * hi[m];
-            yi[i] += v[2 * m] * hi[m];
-            yi[i] += v[2 * m + 1] * hr[m];
-          } else {
-            yr[i] += v[m] * hr[m];
-          }
-        }
+      for (int c = 0; c < NC; ++c) {
+        pj[c] = NlMma<T>::run(u.y[c][i], b[0], pj[c]);
+        if constexpr (CPLX) pj[c] = NlMma<T>::run(nl_rot(u.y[c][i], lane), b[1], pj[c]);
       }
     }
-    if (ok) {
+  };
+  const gptr<T> part = to_global(static_cast<T*>(a.part));
+  // accumulator rows are columns of Y, its columns (lane % 16) atom and projector
+  auto put = [&](int g0) {
+    const int g = g0 + cl / 4;
+    if (g >= np) return;
+    const gptr<T> o = part + (static_cast<int64_t>(p0 + g) * 4 + cl % 4) * a.ldhp;
 #pragma unroll
-      for (int i = 0; i < NPW; ++i) {
-        if (P3 % NW != 0 && i0 + i >= P3) continue;
-        const int64_t r = row(i);
-        Y[r] = yr[i];
-        if constexpr (CPLX) Y[r + 1] = yi[i];
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int j = ctile * (16 * NC) + c * 16 + NlMma<T>::row(i, q);
+        if (j < a.nreal) o[j] = pj[c][i];
       }
+  };
+  Tile ta, tb;
+  auto step = [&](int t, Tile& u) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      if (g < np) add(g, t, hb[g], u);
+#pragma unroll 1
+    for (int g = 4; g < np; ++g) {
+      T h[NC];
+      load_h(g, h);
+      add(g, t, h, u);
     }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (t * 16 + NlMma<T>::row(i, q) < P3) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+          if (ok[c]) Y[u.off[i] * ld + col[c]] = u.y[c][i];
+      }
+    if (a.part) project(0, t, u);
+  };
+  clear();
+  load(0, ta);
+#pragma unroll 1
+  for (int t = 0; t < NT; t += 2) {
+    if (t + 1 < NT) load(t + 1, tb);
+    step(t, ta);
+    if (t + 2 < NT) load(t + 2, ta);
+    if (t + 1 < NT) step(t + 1, tb);
   }
   if (!a.part) return;
-  const gptr<T> part = to_global(static_cast<T*>(a.part));
-  for (int pr = p0; pr < p1; ++pr) {
-    T acc[4 * CF];
-#pragma unroll
-    for (int m = 0; m < 4 * CF; ++m) acc[m] = T(0);
-#pragma unroll
-    for (int i = 0; i < NPW; ++i) {
-      if (P3 % NW != 0 && i0 + i >= P3) continue;
-      const cptr<T> v = val + (static_cast<int64_t>(pr) * P3 + i0 + i) * 4 * CF;
-#pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        if constexpr (CPLX) {   // conj(c) y
-          acc[2 * m] += v[2 * m] * yr[i];
-          acc[2 * m] += v[2 * m + 1] * yi[i];
-          acc[2 * m + 1] += v[2 * m] * yi[i];
-          acc[2 * m + 1] -= v[2 * m + 1] * yr[i];
-        } else {
-          acc[m] += v[m] * yr[i];
-        }
-      }
+  put(0);
+#pragma unroll 1
+  for (int g0 = 4; g0 < np; g0 += 4) {
+    clear();
+#pragma unroll 1
+    for (int t = 0; t < NT; ++t) {
+      load(t, ta);
+      project(g0, t, ta);
     }
-    __syncthreads();   // the previous pair's sums are read
-#pragma unroll
-    for (int m = 0; m < 4 * CF; ++m) red[wave][m][lane] = acc[m];
-    __syncthreads();
-    for (int m = wave; m < 4 * CF; m += NW) {
-      T s = red[0][m][lane];
-#pragma unroll
-      for (int w = 1; w < NW; ++w) s += red[w][m][lane];
-      if (ok) part[(static_cast<int64_t>(pr) * 4 + m / CF) * a.ldhp + static_cast<int64_t>(col) * CF + m % CF] = s;
-    }
+    put(g0);
   }
+}
+
+// Offsets of the owned nodes of a cell from its first (past the end: the last one).
+template <int P> __device__ __forceinline__ void nl_node_offsets(int nc, int32_t* noff) {
+  constexpr int P3 = P * P * P, NT = (P3 + 15) / 16;
+  const int n = nc * P;
+  for (int i = threadIdx.x; i < NT * 16; i += 256) {
+    const int e = i < P3 ? i : P3 - 1;
+    noff[i] = e % P + n * (e / P % P + n * (e / (P * P)));
+  }
+  __syncthreads();
 }
 
 template <int P, typename T, bool CPLX>
-__global__ void __launch_bounds__(512) nl_update_kernel(const NlUpdate a) {
-  nl_update_item<P, T, CPLX>(a, blockIdx.x, blockIdx.y);
+__global__ void __launch_bounds__(256, 4) nl_update_kernel(const NlUpdate a) {
+  __shared__ int32_t noff[(P * P * P + 15) / 16 * 16];
+  nl_node_offsets<P>(a.nc, noff);
+  const int item = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + threadIdx.x / 64);
+  if (item < a.ncells) nl_update_item<P, T, CPLX>(a, item, blockIdx.y, noff);
 }
 
-// hP[atom][m] = h sum over the atom's pairs of their partial projections
+// hP[atom][m] = h sum over the atom's pairs of their partial projections, 64
+// columns per workgroup: 8 waves take every 8th pair, their sums are added in
+// a fixed order.
 template <typename T>
 __device__ __forceinline__ void nl_pair_reduce_item(const NlUpdate& a, const int am, const int jblk) {
+  __shared__ T red[8][64];
   const int at = am / 4, m = am % 4;
-  const int j = jblk * 256 + threadIdx.x;
-  if (j >= a.ldhp) return;
+  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+  const int64_t j = jblk * 64 + lane;   // ldhp is a multiple of 64
   T s = T(0);
   if (j < a.nreal) {
     const gptr<const T> part = to_global(static_cast<const T*>(a.part)) + j + m * a.ldhp;
+    const gptr<const int32_t> list = to_global(a.atom_pair);
     const int e1 = a.atom_pair_ptr[at + 1];
 #pragma unroll 8
-    for (int e = a.atom_pair_ptr[at]; e < e1; ++e) s += part[static_cast<int64_t>(a.atom_pair[e]) * 4 * a.ldhp];
-    s *= static_cast<T>(a.hcoef[am]);
+    for (int e = a.atom_pair_ptr[at] + wave; e < e1; e += 8) s += part[static_cast<int64_t>(list[e]) * 4 * a.ldhp];
   }
-  to_global(static_cast<T*>(a.hP))[static_cast<int64_t>(am) * a.ldhp + j] = s;
+  red[wave][lane] = s;
+  __syncthreads();
+  if (wave != 0) return;
+#pragma unroll
+  for (int w = 1; w < 8; ++w) s += red[w][lane];
+  to_global(static_cast<T*>(a.hP))[static_cast<int64_t>(am) * a.ldhp + j] = s * static_cast<T>(a.hcoef[am]);
 }
 
 template <typename T>
-__global__ void __launch_bounds__(256) nl_pair_reduce_kernel(const NlUpdate a) {
+__global__ void __launch_bounds__(512) nl_pair_reduce_kernel(const NlUpdate a) {
   nl_pair_reduce_item<T>(a, blockIdx.x, blockIdx.y);
 }
 
 template <typename T, bool CPLX>
 hipError_t nl_update_launch(const NlUpdate& a, int p, hipStream_t s) {
-  const dim3 g(a.ncells, (a.ncols + 63) / 64);
+  const dim3 g((a.ncells + 3) / 4, (a.nreal + 16 * kNlGroups - 1) / (16 * kNlGroups));
   if (a.ncells > 0) {
     switch (p) {
-      case 2: hipLaunchKernelGGL((nl_update_kernel<2, T, CPLX>), g, dim3(512), 0, s, a); break;
-      case 3: hipLaunchKernelGGL((nl_update_kernel<3, T, CPLX>), g, dim3(512), 0, s, a); break;
-      case 4: hipLaunchKernelGGL((nl_update_kernel<4, T, CPLX>), g, dim3(512), 0, s, a); break;
-      case 5: hipLaunchKernelGGL((nl_update_kernel<5, T, CPLX>), g, dim3(512), 0, s, a); break;
-      case 6: hipLaunchKernelGGL((nl_update_kernel<6, T, CPLX>), g, dim3(512), 0, s, a); break;
-      case 7: hipLaunchKernelGGL((nl_update_kernel<7, T, CPLX>), g, dim3(512), 0, s, a); break;
+      case 2: hipLaunchKernelGGL((nl_update_kernel<2, T, CPLX>), g, dim3(256), 0, s, a); break;
+      case 3: hipLaunchKernelGGL((nl_update_kernel<3, T, CPLX>), g, dim3(256), 0, s, a); break;
+      case 4: hipLaunchKernelGGL((nl_update_kernel<4, T, CPLX>), g, dim3(256), 0, s, a); break;
+      case 5: hipLaunchKernelGGL((nl_update_kernel<5, T, CPLX>), g, dim3(256), 0, s, a); break;
+      case 6: hipLaunchKernelGGL((nl_update_kernel<6, T, CPLX>), g, dim3(256), 0, s, a); break;
+      case 7: hipLaunchKernelGGL((nl_update_kernel<7, T, CPLX>), g, dim3(256), 0, s, a); break;
       default: return hipErrorInvalidValue;
     }
   }
   if (a.part)
-    hipLaunchKernelGGL((nl_pair_reduce_kernel<T>), dim3(a.natoms * 4, (a.ldhp + 255) / 256), dim3(256), 0, s, a);
+    hipLaunchKernelGGL((nl_pair_reduce_kernel<T>), dim3(a.natoms * 4, a.ldhp / 64), dim3(512), 0, s, a);
   return hipGetLastError();
 }
 

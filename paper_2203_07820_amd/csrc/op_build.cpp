@@ -451,7 +451,8 @@ std::string build_tables(const chfsi_system& sys, HostTables& t) {
     return owns[a].cell != owns[b].cell ? owns[a].cell < owns[b].cell : owns[a].atom < owns[b].atom;
   });
   t.own_atom.resize(owns.size());
-  t.own_val.resize(owns.size() * p3 * vw);
+  const size_t per = (p3 + 15) / 16 * 16 * vw;
+  t.own_val.assign(owns.size() * per, 0.0);
   std::vector<std::vector<int32_t>> of_atom(sys.natoms);
   for (size_t i = 0; i < oo.size(); ++i) {
     const OwnRec& o = owns[oo[i]];
@@ -461,7 +462,10 @@ std::string build_tables(const chfsi_system& sys, HostTables& t) {
     }
     t.own_atom[i] = o.atom;
     of_atom[o.atom].push_back(static_cast<int32_t>(i));
-    std::copy(o.v.begin(), o.v.end(), t.own_val.begin() + i * p3 * vw);
+    for (size_t e = 0; e < p3; ++e)
+      for (int m = 0; m < 4; ++m)
+        for (int c = 0; c < vw / 4; ++c)
+          t.own_val[i * per + ((e / 16 * (vw / 4) + c) * 4 + m) * 16 + e % 16] = o.v[e * vw + m * (vw / 4) + c];
   }
   t.own_ptr.push_back(static_cast<int32_t>(oo.size()));
   for (int at = 0; at < sys.natoms; ++at) {

@@ -1,0 +1,99 @@
+"""H~X by the tensor-product kernel and the nonlocal update that follows it,
+where their tiles end: boxes of 1 to 7 cells per side against x tiles of 2 to
+4 cells, columns around the 16 (FP64) and 32 (FP32) of a lane group and the
+32 of an update wave, odd leading dimensions, degrees of both parities (the
+filter's two buffers), and boxes whose cells hold more than 4 atoms.
+
+Tolerances relative to the largest entry: a filter step sums, per entry, 3(p+1)
+products of 1D factors plus at most a few projectors per atom, each bounded by
+the growth of the step itself, so 1e-12 for one FP64 product and 1e-11 for a
+filter; single precision has 5e8 times the unit roundoff, 2e-5 and 1e-4.
+"""
+import numpy as np
+import pytest
+
+import workloads
+from oracle import chfsi as ochfsi
+from oracle import fe
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():  # pragma: no cover
+    pytest.skip("no GPU", allow_module_level=True)
+
+import paper_2203_07820_amd as lib  # noqa: E402
+
+K = (0.1, -0.2, 0.15)
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = lib.Context(0)
+    yield c
+    c.close()
+
+
+def _relerr(got, want):
+    return float(np.max(np.abs(got - want)) / np.max(np.abs(want)))
+
+
+def _run(ctx, nc, p, atoms, k, ncols, ld, single, m):
+    s = workloads.small_system(nc, p, atoms, seed=10 * nc + p, has_proj=atoms > 0, k=k)
+    op = lib.Operator(ctx, s)
+    H = fe.assemble(fe.build_operator(s))
+    cplx = op.is_complex
+    dt = {(False, False): np.float64, (False, True): np.float32,
+          (True, False): np.complex128, (True, True): np.complex64}[cplx, single]
+    prec = {(False, False): lib.F64, (False, True): lib.F32, (True, False): lib.C128, (True, True): lib.C64}[cplx, single]
+    ncols = min(ncols, op.M)
+    X = workloads.start_block(op.M, ncols, seed=7, complex_=cplx).astype(dt)
+    buf = torch.full((op.M, ld), 3.0, dtype=torch.from_numpy(X).dtype, device="cuda")
+    buf[:, :ncols] = torch.from_numpy(X).cuda()
+    out = torch.full_like(buf, 5.0)
+    ctx.check(ctx.lib.chfsi_apply(op.h, lib._tptr(buf), lib._tptr(out), ncols, ld, prec))
+    torch.cuda.synchronize()
+    Xr = X.astype(np.complex128 if cplx else np.float64)
+    Y = out.cpu().numpy()
+    assert _relerr(Y[:, :ncols], H @ Xr) < (2e-5 if single else 1e-12)
+    assert np.all(Y[:, ncols:] == 5)
+    if single:
+        return
+    b = float(abs(H).sum(axis=1).max())   # an upper bound of the spectrum
+    want = ochfsi.cheb_filter(lambda v: H @ v, Xr, m, 0.3 * b, b, -1.0)
+    ctx.check(ctx.lib.chfsi_filter(op.h, lib._tptr(buf), ncols, ld, m, 0.3 * b, b, -1.0, prec, 0))
+    torch.cuda.synchronize()
+    Y = buf.cpu().numpy()
+    assert _relerr(Y[:, :ncols], want) < 1e-11
+    assert np.all(Y[:, ncols:] == 3)
+
+
+# every order, real and complex, on boxes that end inside an x tile
+@pytest.mark.parametrize("p", [2, 3, 4, 5, 6, 7])
+@pytest.mark.parametrize("nc", [1, 2, 3, 5])
+@pytest.mark.parametrize("k", [(0, 0, 0), K])
+def test_tiles(ctx, p, nc, k):
+    if nc == 5 and p > 5:
+        nc = 4
+    for single in (False, True):
+        _run(ctx, nc, p, 1 if nc > 1 else 0, k, 5, 7, single, 2 + nc % 2)
+
+
+@pytest.mark.parametrize("ncols,ld", [(1, 1), (15, 15), (16, 17), (17, 64), (31, 31), (33, 35), (64, 64), (97, 97)])
+@pytest.mark.parametrize("k", [(0, 0, 0), K])
+def test_columns(ctx, ncols, ld, k):
+    for single in (False, True):
+        _run(ctx, 3, 4, 2, k, ncols, ld, single, 3)
+
+
+# cells with 5 and 9 atoms: the update's own loop and further projection passes
+@pytest.mark.parametrize("atoms", [4, 5, 9])
+@pytest.mark.parametrize("k", [(0, 0, 0), K])
+def test_many_atoms_per_cell(ctx, atoms, k):
+    for single in (False, True):
+        _run(ctx, 2, 5, atoms, k, 18, 18, single, 4)
+
+
+# a mesh of 7 cells per side: tiles of 3 cells are left for tiles of 2
+def test_ragged_wide_tile(ctx):
+    _run(ctx, 7, 4, 2, (0, 0, 0), 20, 20, False, 2)
