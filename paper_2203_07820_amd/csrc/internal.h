@@ -132,6 +132,24 @@ constexpr int kTensorTab = 68 + 8 * 24;
 void pack_tensor_tables(int p, const double* K1, const double* S1, const double* m1, double* out);
 hipError_t launch_tensor_hx(const TensorLaunch& L, int prec, hipStream_t s);
 
+// The same for many problems of one order and precision in one launch.
+// descs: device array of nprob argument blocks (pack_tensor_desc); item_off:
+// device array of nprob + 1 offsets of the problems' workgroups.
+struct TensorBatch {
+  int p;
+  bool wide;                       // tile, tensor_batch_wide() of the problems
+  const void* descs;
+  const int64_t* item_off;
+  int nprob;
+  int64_t nblk;                    // item_off[nprob]
+};
+size_t tensor_desc_bytes(int prec);
+bool tensor_batch_wide(int p, int prec, const std::vector<int>& nc);
+// Writes the argument block of one problem and returns its workgroups; `share`
+// is its part of the launch's work, hence of the device.
+int64_t pack_tensor_desc(const TensorLaunch& L, int prec, bool wide, double share, void* out);
+hipError_t launch_tensor_batched(const TensorBatch& b, int prec, hipStream_t s);
+
 // Many problems of the same order and precision in one persistent launch.
 // descs: device array of nprob packed kernel argument blocks (pack_hx_desc);
 // item_off: device array of nprob + 1 item offsets (items of problem q are
@@ -194,6 +212,22 @@ struct NlUpdate {
   void* part;                       // pairs x 4 x ldhp (real view), or null
 };
 hipError_t launch_nl_update(const NlUpdate& a, int p, int prec, hipStream_t s);
+
+// The update of nprob problems: descs = device array of nprob NlUpdate (part
+// null in all or in none), cell_off / row_off = device arrays of nprob + 1
+// offsets of their workgroups of nl_update_cells() cells and of their (atom,
+// component) rows.
+struct NlUpdateBatch {
+  const void* descs;
+  const int64_t* cell_off;
+  const int64_t* row_off;
+  int nprob;
+  int64_t total_blocks, total_rows;
+  int max_real, max_ldhp;          // widest block in real columns, largest ldhp
+  bool project;                    // part is not null
+};
+int nl_update_cells();
+hipError_t launch_nl_update_batched(const NlUpdateBatch& b, int p, int prec, hipStream_t s);
 
 // Size of the fixed device scratch of chfsi_apply_noalloc() (kernels_nl.hip),
 // and its device address on the current device (call with that device

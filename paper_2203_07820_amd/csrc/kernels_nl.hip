@@ -373,11 +373,27 @@ template <int P> __device__ __forceinline__ void nl_node_offsets(int nc, int32_t
   __syncthreads();
 }
 
+constexpr int kNlCells = 4;    // cells (waves) per workgroup
+
 template <int P, typename T, bool CPLX>
 __global__ void __launch_bounds__(256, 4) nl_update_kernel(const NlUpdate a) {
   __shared__ int32_t noff[(P * P * P + 15) / 16 * 16];
   nl_node_offsets<P>(a.nc, noff);
-  const int item = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + threadIdx.x / 64);
+  const int item = __builtin_amdgcn_readfirstlane(blockIdx.x * kNlCells + threadIdx.x / 64);
+  if (item < a.ncells) nl_update_item<P, T, CPLX>(a, item, blockIdx.y, noff);
+}
+
+// The update of many problems (batched filter): descriptors in device memory.
+template <int P, typename T, bool CPLX>
+__global__ void __launch_bounds__(256, 4)
+nl_update_batched_kernel(const NlUpdate* __restrict__ d, const int64_t* __restrict__ cell_off, const int nprob) {
+  __shared__ int32_t noff[(P * P * P + 15) / 16 * 16];
+  const int q = __builtin_amdgcn_readfirstlane(problem_of(cell_off, nprob, blockIdx.x));
+  const NlUpdate& a = d[q];
+  if (static_cast<int>(blockIdx.y) * 16 * kNlGroups >= a.nreal) return;
+  nl_node_offsets<P>(a.nc, noff);
+  const int item =
+      __builtin_amdgcn_readfirstlane(static_cast<int>(blockIdx.x - cell_off[q]) * kNlCells + threadIdx.x / 64);
   if (item < a.ncells) nl_update_item<P, T, CPLX>(a, item, blockIdx.y, noff);
 }
 
@@ -411,9 +427,18 @@ __global__ void __launch_bounds__(512) nl_pair_reduce_kernel(const NlUpdate a) {
   nl_pair_reduce_item<T>(a, blockIdx.x, blockIdx.y);
 }
 
+template <typename T>
+__global__ void __launch_bounds__(512)
+nl_pair_reduce_batched_kernel(const NlUpdate* __restrict__ d, const int64_t* __restrict__ row_off, const int nprob) {
+  const int q = __builtin_amdgcn_readfirstlane(problem_of(row_off, nprob, blockIdx.x));
+  const NlUpdate& a = d[q];
+  if (static_cast<int64_t>(blockIdx.y) * 64 >= a.ldhp) return;
+  nl_pair_reduce_item<T>(a, static_cast<int>(blockIdx.x - row_off[q]), blockIdx.y);
+}
+
 template <typename T, bool CPLX>
 hipError_t nl_update_launch(const NlUpdate& a, int p, hipStream_t s) {
-  const dim3 g((a.ncells + 3) / 4, (a.nreal + 16 * kNlGroups - 1) / (16 * kNlGroups));
+  const dim3 g((a.ncells + kNlCells - 1) / kNlCells, (a.nreal + 16 * kNlGroups - 1) / (16 * kNlGroups));
   if (a.ncells > 0) {
     switch (p) {
       case 2: hipLaunchKernelGGL((nl_update_kernel<2, T, CPLX>), g, dim3(256), 0, s, a); break;
@@ -427,6 +452,27 @@ hipError_t nl_update_launch(const NlUpdate& a, int p, hipStream_t s) {
   }
   if (a.part)
     hipLaunchKernelGGL((nl_pair_reduce_kernel<T>), dim3(a.natoms * 4, a.ldhp / 64), dim3(512), 0, s, a);
+  return hipGetLastError();
+}
+
+template <typename T, bool CPLX>
+hipError_t nl_update_batched(const NlUpdateBatch& b, int p, hipStream_t s) {
+  const NlUpdate* d = static_cast<const NlUpdate*>(b.descs);
+  const dim3 g(static_cast<unsigned>(b.total_blocks), (b.max_real + 16 * kNlGroups - 1) / (16 * kNlGroups));
+  if (b.total_blocks > 0) {
+    switch (p) {
+      case 2: hipLaunchKernelGGL((nl_update_batched_kernel<2, T, CPLX>), g, dim3(256), 0, s, d, b.cell_off, b.nprob); break;
+      case 3: hipLaunchKernelGGL((nl_update_batched_kernel<3, T, CPLX>), g, dim3(256), 0, s, d, b.cell_off, b.nprob); break;
+      case 4: hipLaunchKernelGGL((nl_update_batched_kernel<4, T, CPLX>), g, dim3(256), 0, s, d, b.cell_off, b.nprob); break;
+      case 5: hipLaunchKernelGGL((nl_update_batched_kernel<5, T, CPLX>), g, dim3(256), 0, s, d, b.cell_off, b.nprob); break;
+      case 6: hipLaunchKernelGGL((nl_update_batched_kernel<6, T, CPLX>), g, dim3(256), 0, s, d, b.cell_off, b.nprob); break;
+      case 7: hipLaunchKernelGGL((nl_update_batched_kernel<7, T, CPLX>), g, dim3(256), 0, s, d, b.cell_off, b.nprob); break;
+      default: return hipErrorInvalidValue;
+    }
+  }
+  if (b.project && b.total_rows > 0)
+    hipLaunchKernelGGL((nl_pair_reduce_batched_kernel<T>), dim3(static_cast<unsigned>(b.total_rows), b.max_ldhp / 64),
+                       dim3(512), 0, s, d, b.row_off, b.nprob);
   return hipGetLastError();
 }
 
@@ -490,6 +536,18 @@ hipError_t launch_nl_update(const NlUpdate& a, int p, int prec, hipStream_t s) {
     case CHFSI_F32: return nl_update_launch<float, false>(a, p, s);
     case CHFSI_C128: return nl_update_launch<double, true>(a, p, s);
     case CHFSI_C64: return nl_update_launch<float, true>(a, p, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+int nl_update_cells() { return kNlCells; }
+
+hipError_t launch_nl_update_batched(const NlUpdateBatch& b, int p, int prec, hipStream_t s) {
+  switch (prec) {
+    case CHFSI_F64: return nl_update_batched<double, false>(b, p, s);
+    case CHFSI_F32: return nl_update_batched<float, false>(b, p, s);
+    case CHFSI_C128: return nl_update_batched<double, true>(b, p, s);
+    case CHFSI_C64: return nl_update_batched<float, true>(b, p, s);
     default: return hipErrorInvalidValue;
   }
 }

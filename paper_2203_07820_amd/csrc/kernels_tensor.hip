@@ -38,6 +38,7 @@
 
 #include <algorithm>
 
+#include "device_util.h"
 #include "internal.h"
 
 namespace chfsi {
@@ -536,11 +537,17 @@ template <int P, typename T, bool CPLX, int TX>
 __global__ void __attribute__((amdgpu_flat_work_group_size(64 * TsShape<P, T, CPLX, TX>::WAVES,
                                                            64 * TsShape<P, T, CPLX, TX>::WAVES),
                                amdgpu_waves_per_eu(TsShape<P, T, CPLX, TX>::WPE)))
-tensor_hx_kernel(const TsArgs<T> kernel_args) {
+tensor_hx_kernel(const TsArgs<T> kernel_args, const TsArgs<T>* descs, const int64_t* item_off, const int nprob) {
   using Sh = TsShape<P, T, CPLX, TX>;
   __shared__ typename Lane<T>::V lds[2 * Sh::LBUF];
-  const cptr<TsArgs<T>> args = (cptr<TsArgs<T>>)__builtin_amdgcn_kernarg_segment_ptr();
-  ts_workgroup<P, T, CPLX, TX>(args, xcd_order(blockIdx.x, gridDim.x), lds);
+  int w = xcd_order(blockIdx.x, gridDim.x);
+  cptr<TsArgs<T>> args = (cptr<TsArgs<T>>)__builtin_amdgcn_kernarg_segment_ptr();
+  if (nprob > 0) {   // the arguments come first in the segment; a batch has them in a device table
+    const int q = __builtin_amdgcn_readfirstlane(problem_of(item_off, nprob, w));
+    w -= static_cast<int>(item_off[q]);
+    args = to_const(descs + q);
+  }
+  ts_workgroup<P, T, CPLX, TX>(args, w, lds);
 }
 
 // Cells per chunk in z.  A chunk repeats the planes of the cell below it, so
@@ -563,7 +570,7 @@ int chunk_cells(int64_t columns, int nc, int slots) {
 
 // Workgroups of one problem and its argument block.
 template <int P, typename T, bool CPLX, int TX>
-int64_t ts_pack(const TensorLaunch& L, TsArgs<T>& a) {
+int64_t ts_pack(const TensorLaunch& L, double share, TsArgs<T>& a) {
   using Sh = TsShape<P, T, CPLX, TX>;
   a.Xk = static_cast<const T*>(L.Xk);
   a.Xp = static_cast<const T*>(L.Xp ? L.Xp : L.Xk);
@@ -585,19 +592,8 @@ int64_t ts_pack(const TensorLaunch& L, TsArgs<T>& a) {
   a.sz = static_cast<T>(L.kh[2]);
   constexpr int NCOL = kL * 8 / static_cast<int>(sizeof(T));
   const int64_t columns = static_cast<int64_t>((L.ncols + NCOL - 1) / NCOL) * L.nc * ((L.nc + TX - 1) / TX);
-  a.nz = chunk_cells(columns, L.nc, std::max(1, L.ncu) * Sh::NWG);
+  a.nz = chunk_cells(columns, L.nc, std::max(1, static_cast<int>(share * L.ncu * Sh::NWG)));
   return columns * ((L.nc + a.nz - 1) / a.nz);
-}
-
-template <int P, typename T, bool CPLX, int TX>
-hipError_t ts_launch(const TensorLaunch& L, hipStream_t s) {
-  TsArgs<T> a;
-  const int64_t nblk = ts_pack<P, T, CPLX, TX>(L, a);
-  if (nblk <= 0) return hipSuccess;
-  if (nblk > 0x7fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((tensor_hx_kernel<P, T, CPLX, TX>), dim3(static_cast<unsigned>(nblk)),
-                     dim3(64 * TsShape<P, T, CPLX, TX>::WAVES), 0, s, a);
-  return hipGetLastError();
 }
 
 // Cells in x per workgroup: a wide tile reads fewer neighbour nodes per owned
@@ -605,29 +601,54 @@ hipError_t ts_launch(const TensorLaunch& L, hipStream_t s) {
 // 2.71 ms in FP64, 1.31 against 1.53 ms in FP32), as far as the LDS and, for
 // complex p = 6, the registers allow; two cells where the wide tile would
 // leave more than an eighth of its cells beyond the mesh.
-template <int P, typename T, bool CPLX> constexpr int wide_tile() {
-  return P <= 3 ? 4 : (P <= 5 || (P == 6 && !CPLX) ? 3 : 2);
-}
-inline bool use_wide(int nc, int wide) { return (nc + wide - 1) / wide * wide * 8 <= (nc + 1) / 2 * 2 * 9; }
-
-template <int P, typename T, bool CPLX>
-hipError_t ts_launch_tile(const TensorLaunch& L, hipStream_t s) {
-  constexpr int W = wide_tile<P, T, CPLX>();
-  if (W > 2 && !use_wide(L.nc, W)) return ts_launch<P, T, CPLX, 2>(L, s);
-  return ts_launch<P, T, CPLX, W>(L, s);
-}
-
-template <typename T, bool CPLX>
-hipError_t ts_launch_p(const TensorLaunch& L, hipStream_t s) {
-  switch (L.p) {
-    case 2: return ts_launch_tile<2, T, CPLX>(L, s);
-    case 3: return ts_launch_tile<3, T, CPLX>(L, s);
-    case 4: return ts_launch_tile<4, T, CPLX>(L, s);
-    case 5: return ts_launch_tile<5, T, CPLX>(L, s);
-    case 6: return ts_launch_tile<6, T, CPLX>(L, s);
-    case 7: return ts_launch_tile<7, T, CPLX>(L, s);
-    default: return hipErrorInvalidValue;
+constexpr int wide_tile(int p, bool cplx) { return p <= 3 ? 4 : (p <= 5 || (p == 6 && !cplx) ? 3 : 2); }
+inline bool use_wide(const int* nc, int n, int wide) {
+  double w = 0, two = 0;
+  for (int i = 0; i < n; ++i) {
+    const double rows = static_cast<double>(nc[i]) * nc[i];
+    w += rows * ((nc[i] + wide - 1) / wide * wide);
+    two += rows * ((nc[i] + 1) / 2 * 2);
   }
+  return w * 8 <= two * 9;
+}
+
+// f(Tag) with the kernel's template arguments.
+template <int P, typename T, bool CPLX, int TX> struct TsTag {
+  typedef T real;
+  static int64_t pack(const TensorLaunch& L, double share, TsArgs<T>& a) { return ts_pack<P, T, CPLX, TX>(L, share, a); }
+  static hipError_t launch(int64_t nblk, const TsArgs<T>& a, const TsArgs<T>* descs, const int64_t* off, int nprob,
+                           hipStream_t s) {
+    if (nblk <= 0) return hipSuccess;
+    if (nblk > 0x7fffffff) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((tensor_hx_kernel<P, T, CPLX, TX>), dim3(static_cast<unsigned>(nblk)),
+                       dim3(64 * TsShape<P, T, CPLX, TX>::WAVES), 0, s, a, descs, off, nprob);
+    return hipGetLastError();
+  }
+};
+template <int P, typename T, bool CPLX, typename F> auto ts_tile(bool wide, F f) {
+  constexpr int W = wide_tile(P, CPLX);
+  return wide ? f(TsTag<P, T, CPLX, W>{}) : f(TsTag<P, T, CPLX, 2>{});
+}
+template <typename T, bool CPLX, typename F> auto ts_order(int p, bool wide, F f) {
+  switch (p) {
+    case 2: return ts_tile<2, T, CPLX>(wide, f);
+    case 3: return ts_tile<3, T, CPLX>(wide, f);
+    case 4: return ts_tile<4, T, CPLX>(wide, f);
+    case 5: return ts_tile<5, T, CPLX>(wide, f);
+    case 6: return ts_tile<6, T, CPLX>(wide, f);
+    default: return ts_tile<7, T, CPLX>(wide, f);
+  }
+}
+template <typename F> auto ts_dispatch(int p, int prec, bool wide, F f) {
+  switch (prec) {
+    case CHFSI_F64: return ts_order<double, false>(p, wide, f);
+    case CHFSI_F32: return ts_order<float, false>(p, wide, f);
+    case CHFSI_C128: return ts_order<double, true>(p, wide, f);
+    default: return ts_order<float, true>(p, wide, f);
+  }
+}
+bool ts_valid(int p, int prec) {
+  return p >= 2 && p <= 7 && (prec == CHFSI_F64 || prec == CHFSI_F32 || prec == CHFSI_C128 || prec == CHFSI_C64);
 }
 
 }  // namespace
@@ -655,13 +676,37 @@ void pack_tensor_tables(int p, const double* K1, const double* S1, const double*
 }
 
 hipError_t launch_tensor_hx(const TensorLaunch& L, int prec, hipStream_t s) {
-  switch (prec) {
-    case CHFSI_F64: return ts_launch_p<double, false>(L, s);
-    case CHFSI_F32: return ts_launch_p<float, false>(L, s);
-    case CHFSI_C128: return ts_launch_p<double, true>(L, s);
-    case CHFSI_C64: return ts_launch_p<float, true>(L, s);
-    default: return hipErrorInvalidValue;
-  }
+  if (!ts_valid(L.p, prec)) return hipErrorInvalidValue;
+  return ts_dispatch(L.p, prec, tensor_batch_wide(L.p, prec, {L.nc}), [&](auto tag) {
+    typedef decltype(tag) Tag;
+    TsArgs<typename Tag::real> a;
+    const int64_t nblk = Tag::pack(L, 1.0, a);
+    return Tag::launch(nblk, a, nullptr, nullptr, 0, s);
+  });
+}
+
+size_t tensor_desc_bytes(int prec) {
+  return prec == CHFSI_F64 || prec == CHFSI_C128 ? sizeof(TsArgs<double>) : sizeof(TsArgs<float>);
+}
+
+bool tensor_batch_wide(int p, int prec, const std::vector<int>& nc) {
+  return use_wide(nc.data(), static_cast<int>(nc.size()), wide_tile(p, prec == CHFSI_C128 || prec == CHFSI_C64));
+}
+
+int64_t pack_tensor_desc(const TensorLaunch& L, int prec, bool wide, double share, void* out) {
+  return ts_dispatch(L.p, prec, wide, [&](auto tag) {
+    typedef decltype(tag) Tag;
+    return Tag::pack(L, share, *static_cast<TsArgs<typename Tag::real>*>(out));
+  });
+}
+
+hipError_t launch_tensor_batched(const TensorBatch& b, int prec, hipStream_t s) {
+  if (!ts_valid(b.p, prec)) return hipErrorInvalidValue;
+  return ts_dispatch(b.p, prec, b.wide, [&](auto tag) {
+    typedef decltype(tag) Tag;
+    typedef TsArgs<typename Tag::real> A;
+    return Tag::launch(b.nblk, A{}, static_cast<const A*>(b.descs), b.item_off, b.nprob, s);
+  });
 }
 
 }  // namespace chfsi
