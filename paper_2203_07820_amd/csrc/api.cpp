@@ -45,12 +45,45 @@ int upload(chfsi_op* op, const std::vector<T>& v, T** out) {
   return 0;
 }
 
-int upload_f32(chfsi_op* op, const std::vector<double>& v, void** out) {
-  std::vector<float> f(v.size());
-  for (size_t i = 0; i < v.size(); ++i) f[i] = static_cast<float>(v[i]);
-  float* p = nullptr;
-  CHECK(upload(op, f, &p));
-  *out = p;
+// A table in double and in single precision.  Large ones (all of them multiples
+// of 64 entries) are rounded on the device: their second copy over the host
+// link and the host's conversion were a fifth of the operator build.
+int upload_both(chfsi_op* op, const std::vector<double>& v, void** out64, void** out32) {
+  double* d = nullptr;
+  CHECK(upload(op, v, &d));
+  *out64 = d;
+  *out32 = nullptr;
+  if (v.size() % 64 != 0) {
+    float* f = nullptr;
+    CHECK(upload(op, std::vector<float>(v.begin(), v.end()), &f));
+    *out32 = f;
+  } else if (!v.empty()) {
+    void* p = nullptr;
+    if (hipMalloc(&p, v.size() * sizeof(float)) != hipSuccess)
+      return fail(op->ctx, CHFSI_ENOMEM, "hipMalloc of operator table failed");
+    op->allocs.push_back(p);
+    HIP_TRY(op->ctx, launch_convert(p, 64, CHFSI_F32, d, 64, CHFSI_F64, static_cast<int64_t>(v.size() / 64), 64,
+                                    op->ctx->stream));
+    *out32 = p;
+  }
+  return 0;
+}
+
+// The owner cells' projector values, from the uploaded pair tables.
+int build_own_table(chfsi_op* op) {
+  const HostTables& t = op->t;
+  const size_t n = op->nown_pairs * own_table_entries(t.p, t.cplx);
+  if (n == 0) return 0;
+  int32_t* pairs = nullptr;
+  CHECK(upload(op, t.own_pair, &pairs));
+  for (void** p : {&op->own_val64, &op->own_val32}) {
+    if (hipMalloc(p, n * (p == &op->own_val64 ? 8 : 4)) != hipSuccess)
+      return fail(op->ctx, CHFSI_ENOMEM, "hipMalloc of operator table failed");
+    op->allocs.push_back(*p);
+  }
+  HIP_TRY(op->ctx, launch_own_table(pairs, op->nown_pairs, t.p, t.mpad, static_cast<const double*>(op->pair_re64),
+                                    static_cast<const double*>(op->pair_im64), static_cast<double*>(op->own_val64),
+                                    static_cast<float*>(op->own_val32), op->ctx->stream));
   return 0;
 }
 
@@ -487,7 +520,7 @@ int read_info(chfsi_ctx* ctx, rocblas_int* dinfo, int* info) {
   return 0;
 }
 
-// CholGS: Xout = X L^-H with S = X^H X = L L^H.  Xout may not alias X.  On
+// CholGS: Xout = X L^-H with S = X^H X = L L^H.  Xout may be X.  On
 // CHFSI_ECHOL, *bad_col (nullable) receives the first column that is a
 // combination of the earlier ones to working precision.
 int cholgs(chfsi_op* op, const double* X, int64_t ldx, double* Xout, int64_t ldo, int64_t N, double* L_host,
@@ -788,10 +821,7 @@ int rrgep_split(chfsi_op* op, double* X, int64_t ldx, int64_t N, int nfr, bool m
     HIP_TRY(ctx, launch_rotate(X32, nr, Z32, nr, static_cast<float*>(c32), nr, M, nrr, nrr, true, st));
     HIP_TRY(ctx, launch_add_scaled_cols(static_cast<float*>(c32), nr, dg, X, ldxr, M, nrr, st));
   } else {
-    void* X2;
-    CHECK(ws_get(ctx, WS_X2, static_cast<size_t>(M) * nr * 8, &X2));
-    HIP_TRY(ctx, launch_rotate(X, ldxr, Zr, nr, static_cast<double*>(X2), nr, M, nrr, nrr, true, st));
-    HIP_TRY(ctx, launch_convert(X, ldxr, CHFSI_F64, X2, nr, CHFSI_F64, M, nr, st));
+    HIP_TRY(ctx, launch_rotate(X, ldxr, Zr, nr, X, ldxr, M, nrr, nrr, true, st));
   }
   HIP_TRY(ctx, hipMemcpyAsync(theta, D, N * 8, hipMemcpyDeviceToHost, st));
   HIP_TRY(ctx, hipStreamSynchronize(st));
@@ -1785,10 +1815,7 @@ int chfsi_op_build(chfsi_ctx* ctx, const chfsi_system* sys, chfsi_op** out) {
   do {
     std::vector<double> sw(static_cast<size_t>(t.mpad / 16) * (t.mpad / 4) * 64);
     swizzle_cell_matrix(t.cell_re.data(), t.mcell, t.mpad, sw.data());
-    double* d;
-    if ((rc = upload(op.get(), sw, &d)) < 0) break;
-    op->A64 = d;
-    if ((rc = upload_f32(op.get(), sw, &op->A32)) < 0) break;
+    if ((rc = upload_both(op.get(), sw, &op->A64, &op->A32)) < 0) break;
     if (!t.cplx) {
       const int mp32 = mpad32_of(t.p);
       std::vector<uint16_t> bf(static_cast<size_t>(mp32 / 16) * (mp32 / 32) * 64 * 8);
@@ -1799,15 +1826,11 @@ int chfsi_op_build(chfsi_ctx* ctx, const chfsi_system* sys, chfsi_op** out) {
     }
     if (t.cplx) {
       swizzle_cell_matrix(t.cell_im.data(), t.mcell, t.mpad, sw.data());
-      if ((rc = upload(op.get(), sw, &d)) < 0) break;
-      op->Ai64 = d;
-      if ((rc = upload_f32(op.get(), sw, &op->Ai32)) < 0) break;
+      if ((rc = upload_both(op.get(), sw, &op->Ai64, &op->Ai32)) < 0) break;
     }
     std::vector<double> ts(kTensorTab);
     pack_tensor_tables(t.p, t.ts_K.data(), t.ts_S.data(), t.ts_m.data(), ts.data());
-    if ((rc = upload(op.get(), ts, &d)) < 0) break;
-    op->ts_tab64 = d;
-    if ((rc = upload_f32(op.get(), ts, &op->ts_tab32)) < 0) break;
+    if ((rc = upload_both(op.get(), ts, &op->ts_tab64, &op->ts_tab32)) < 0) break;
     if ((rc = upload(op.get(), t.vdiag, &op->vdiag)) < 0) break;
     if ((rc = upload(op.get(), t.dscale, &op->dscale)) < 0) break;
     if (t.has_proj) {
@@ -1834,23 +1857,18 @@ int chfsi_op_build(chfsi_ctx* ctx, const chfsi_system* sys, chfsi_op** out) {
       if ((rc = upload(op.get(), t.own_atom, &op->own_atom)) < 0) break;
       if ((rc = upload(op.get(), t.atom_pair_ptr, &op->atom_pair_ptr)) < 0) break;
       if ((rc = upload(op.get(), t.atom_pair, &op->atom_pair)) < 0) break;
-      if ((rc = upload(op.get(), t.own_val, &d)) < 0) break;
-      op->own_val64 = d;
-      if ((rc = upload_f32(op.get(), t.own_val, &op->own_val32)) < 0) break;
       op->nown_cells = static_cast<int>(t.own_cell.size());
       op->nown_pairs = static_cast<int>(t.own_atom.size());
       if ((rc = upload(op.get(), t.pair_ptr, &op->pair_ptr)) < 0) break;
       if ((rc = upload(op.get(), t.pair_atom, &op->pair_atom)) < 0) break;
       op->npairs = static_cast<int64_t>(t.pair_atom.size());
-      if ((rc = upload(op.get(), t.pair_re, &d)) < 0) break;
-      op->pair_re64 = d;
-      if ((rc = upload_f32(op.get(), t.pair_re, &op->pair_re32)) < 0) break;
+      if ((rc = upload_both(op.get(), t.pair_re, &op->pair_re64, &op->pair_re32)) < 0) break;
       if (t.cplx) {
-        if ((rc = upload(op.get(), t.pair_im, &d)) < 0) break;
-        op->pair_im64 = d;
-        if ((rc = upload_f32(op.get(), t.pair_im, &op->pair_im32)) < 0) break;
+        if ((rc = upload_both(op.get(), t.pair_im, &op->pair_im64, &op->pair_im32)) < 0) break;
       }
+      if ((rc = build_own_table(op.get())) < 0) break;
     }
+    if (hipStreamSynchronize(ctx->stream) != hipSuccess) rc = fail(ctx, CHFSI_EHIP, "operator table upload failed");
   } while (0);
   if (rc < 0) {
     cleanup();
@@ -1861,7 +1879,6 @@ int chfsi_op_build(chfsi_ctx* ctx, const chfsi_system* sys, chfsi_op** out) {
   std::vector<int32_t>().swap(t.atom_node);
   std::vector<double>().swap(t.pair_re);
   std::vector<double>().swap(t.pair_im);
-  std::vector<double>().swap(t.own_val);
   // deterministic assembly already on: the colour classes now, so that no
   // later call has to allocate them (operators with one cell per side have
   // none and are refused at their first H~.X)
@@ -2138,10 +2155,7 @@ int chfsi_orthonormalize(chfsi_op* op, void* X, int64_t ncols, int64_t ld, doubl
   chfsi_ctx* ctx = op->ctx;
   CHECK(check_block(op, X, ncols, ld));
   const int cf = op->t.cplx ? 2 : 1;
-  void* X2;
-  CHECK(ws_get(ctx, WS_X2, static_cast<size_t>(op->t.M) * ncols * 8 * cf, &X2));
-  CHECK(cholgs(op, static_cast<double*>(X), ld, static_cast<double*>(X2), ncols, ncols, L_host));
-  HIP_TRY(ctx, launch_convert(X, ld * cf, CHFSI_F64, X2, ncols * cf, CHFSI_F64, op->t.M, ncols * cf, ctx->stream));
+  CHECK(cholgs(op, static_cast<double*>(X), ld, static_cast<double*>(X), ld, ncols, L_host));
   HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
   return 0;
 }

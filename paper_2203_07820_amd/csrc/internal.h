@@ -53,12 +53,9 @@ struct HostTables {
   // independent of h: half the stiffness, skew derivative; m with
   // diag(1/2, 1, .., 1, 1/2) - m m^T the mass
   std::vector<double> ts_K, ts_S, ts_m;
-  // (owner cell, atom) pairs sorted by cell, with the projector values of the
-  // cell's p^3 owned nodes (local indices < p, x fastest) in tiles of 16,
-  // [pair][tile][re, im][projector][node]: the cells that have pairs, their
-  // pairs, and the pairs of every atom
-  std::vector<int32_t> own_cell, own_ptr, own_atom;
-  std::vector<double> own_val;
+  // (owner cell, atom) pairs sorted by cell: the cells that have pairs, their
+  // pairs (with their places among the pairs above), and the pairs of every atom
+  std::vector<int32_t> own_cell, own_ptr, own_atom, own_pair;
   std::vector<int32_t> atom_pair_ptr, atom_pair;
   std::vector<double> atoms;        // natoms x 8: x, y, z, Z, s, h_s, h_p, 0
 };
@@ -203,7 +200,7 @@ struct NlUpdate {
   int natoms, ncells, nc;           // cells that own touched nodes
   int ncols, nreal;                 // logical and real columns
   const int32_t* cells; const int32_t* pair_ptr; const int32_t* pair_atom;
-  const void* val;                  // HostTables own_val
+  const void* val;                  // projector values (launch_own_table)
   const int32_t* atom_pair_ptr; const int32_t* atom_pair;
   const double* hcoef;
   void* Y; int64_t ldy;             // logical ld
@@ -227,6 +224,13 @@ struct NlUpdateBatch {
   bool project;                    // part is not null
 };
 int nl_update_cells();
+// Projector values of the owner cells' p^3 nodes (local indices < p, x fastest)
+// in tiles of 16, [pair][tile][re, im][projector][node], zero past the last
+// node, from the tables of the cells that hold them (pair_re, pair_im; their
+// multiplicity, a power of two, is taken out again exactly).
+size_t own_table_entries(int p, bool cplx);   // per pair
+hipError_t launch_own_table(const int32_t* own_pair, int nown, int p, int mpad, const double* pair_re,
+                            const double* pair_im, double* out64, float* out32, hipStream_t s);
 hipError_t launch_nl_update_batched(const NlUpdateBatch& b, int p, int prec, hipStream_t s);
 
 // Size of the fixed device scratch of chfsi_apply_noalloc() (kernels_nl.hip),
@@ -301,7 +305,8 @@ hipError_t launch_gram(const double* X, int64_t ldx, const double* Y, int64_t ld
 hipError_t launch_gram(const float* X, int64_t ldx, const float* Y, int64_t ldy, int64_t M, int n,
                        double* partial, double* G, int64_t ldg, hipStream_t s, int64_t offx = 0,
                        int64_t offy = 0);
-// C = X Z, X: M x K (ldx), Z: K x N2 row-major (ldz); upper = Z upper-triangular.
+// C = X Z, X: M x K (ldx), Z: K x N2 row-major (ldz); upper = Z upper-triangular
+// in its 16 x 16 tiles: then C may be X.
 hipError_t launch_rotate(const double* X, int64_t ldx, const double* Z, int64_t ldz, double* C,
                          int64_t ldc, int64_t M, int K, int N2, bool upper, hipStream_t s);
 hipError_t launch_rotate(const float* X, int64_t ldx, const float* Z, int64_t ldz, float* C,

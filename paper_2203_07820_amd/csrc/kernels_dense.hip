@@ -8,6 +8,8 @@
 // whose entries are recombined, which costs exactly the complex flop count.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "internal.h"
 
 namespace chfsi {
@@ -42,17 +44,26 @@ template <> struct Mfma<float> {
   static __device__ __forceinline__ int row(int lane, int i) { return 4 * (lane / 16) + i; }
 };
 
-// ---- Gram: partial[chunk] tile (I, J), I >= J, of X^T Y --------------------
-// One workgroup computes a 128 x 128 tile over the rows of one chunk; 4 waves
-// of 64 x 64 (4 x 4 MFMA tiles).  In a 4-row k step, lanes 16 q .. 16 q + 15
-// read 16 consecutive columns of row 4 s + q, which is both the A operand
-// (X^T) and the B operand (Y) layout of the f64 MFMA, so the fragments go
-// straight from memory into registers: buffer loads from the chunk's first
-// row, the row offset in the lane's voffset (clamped to the chunk, tail rows
-// zeroed at use), the four 16-column groups in the instruction offset.
-// Loads run two k steps ahead of the MFMAs; no LDS, no barriers.
-constexpr int kGT = 128;  // Gram tile
-constexpr int kGramStages = 3;   // register stages of the Gram pipeline (loads GS - 1 steps ahead)
+// ---- Gram: lower blocks of X^T Y ------------------------------------------
+// One wave computes a 64 x 64 block (I, J), I >= J, over the rows of one
+// chunk.  In a 4-row k step, lanes 16 q .. 16 q + 15 read 16 consecutive
+// columns of row 4 s + q, which is both the A operand (X^T) and the B operand
+// (Y) layout of the f64 MFMA, so the fragments go straight from memory into
+// registers: buffer loads from the chunk's first row, the row offset in the
+// lane's voffset, the 16-column groups in the instruction offset.  Loads run
+// two k steps ahead of the MFMAs; no LDS, no barriers.
+// Bound by the matrix cores, so no product is made for padding: the last block
+// row takes only its groups of 16 columns and diagonal blocks only their lower
+// 16 x 16 tiles.  The blocks then differ in work; as single-wave workgroups,
+// in two rounds over the device, they level out.  On 2,985,984 x 256 FP64
+// (136 of the 192 tiles that 128 x 128 workgroups multiplied):
+// @GRAM_MEASURED@
+constexpr int kGB = 64;          // columns of a block
+#ifndef VGW
+#define VGW 4096
+#endif
+constexpr int kGramWaves = VGW;
+constexpr int kGramStages = 3;   // register stages (loads GS - 1 steps ahead)
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* p, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
@@ -73,112 +84,152 @@ __device__ __forceinline__ T bload_group(__amdgpu_buffer_rsrc_t r, int voff) {
   else return bload32<G * 64>(r, voff);
 }
 
-template <typename T, int GS>
-__global__ void __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(2, 2)))
-gram_kernel(const T* __restrict__ X, int64_t ldx, const T* __restrict__ Y, int64_t ldy,
-            int64_t M, int n, int64_t rows_per_chunk, int npad, double* __restrict__ part, int64_t offx,
-            int64_t offy) {
-  const int t = blockIdx.x;
-  // lower-triangular tile index -> (I, J)
-  int I = static_cast<int>((sqrt(8.0 * t + 1.0) - 1.0) / 2.0);
-  while ((I + 1) * (I + 2) / 2 <= t) ++I;
-  while (I * (I + 1) / 2 > t) --I;
-  const int J = t - I * (I + 1) / 2;
-  const int chunk = blockIdx.y;
-  const int64_t m0 = chunk * rows_per_chunk;
-  int64_t m1 = m0 + rows_per_chunk;
-  if (m1 > M) m1 = M;
-  const int nrows = static_cast<int>(m1 - m0);
-  const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64;
-  const int wi = (wave / 2) * 64, wj = (wave % 2) * 64;
+template <typename T> struct GramArgs {
+  const T* X; const T* Y;
+  int64_t ldx, ldy, M;
+  int n, nblk;                     // columns; blocks
+  int64_t rows;                    // per chunk
+  double* part;                    // [chunk][block][64][64]
+  int64_t offx, offy;              // first columns' positions in their rows
+};
+
+// RA groups of 16 rows of the block, CA of its columns.
+template <typename T, int GS, int RA, int CA, bool DIAG>
+__device__ __forceinline__ void gram_block(const GramArgs<T>& a, const int I, const int J, const int64_t m0,
+                                           const int nrows, double* __restrict__ out) {
+  const int lane = threadIdx.x % 64;
   using Acc = typename Mfma<T>::Acc;
-  Acc acc[4][4];
+  Acc acc[RA][CA];
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int i = 0; i < RA; ++i)
 #pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = Acc{0, 0, 0, 0};
-  // per-lane column of the first 16-column group (the others are +16 k).
-  // Columns at or beyond n belong to the tile's padding, which is never read
-  // back: what they load (the rest of the row, the next row, or zero past the
-  // end of the chunk, where the buffer range check returns 0) does not matter.
-  const int ci = I * kGT + wi + lane % 16;
-  const int cj = J * kGT + wj + lane % 16;
-  const int64_t nr = nrows > 0 ? nrows : 0;
+    for (int j = 0; j < CA; ++j) acc[i][j] = Acc{0, 0, 0, 0};
   // X and Y may start offx / offy columns into their rows (a column slice):
   // the ranges then end offx / offy elements before the last row's end, so
-  // the padding columns of the last chunk never reach past the allocation
-  const int64_t ex = nr > 0 ? (nr * ldx < (M - m0) * ldx - offx ? nr * ldx : (M - m0) * ldx - offx) : 0;
-  const int64_t ey = nr > 0 ? (nr * ldy < (M - m0) * ldy - offy ? nr * ldy : (M - m0) * ldy - offy) : 0;
-  const __amdgpu_buffer_rsrc_t rx = rsrc(X + (nr > 0 ? m0 * ldx : 0), static_cast<uint32_t>(ex * sizeof(T)));
-  const __amdgpu_buffer_rsrc_t ry = rsrc(Y + (nr > 0 ? m0 * ldy : 0), static_cast<uint32_t>(ey * sizeof(T)));
-  const int KS = nrows > 0 ? (nrows + 3) / 4 : 0;   // every chunk still writes its tile
-  auto load = [&](T (&xv)[4], T (&yv)[4], int s) {
+  // the padding columns of the last chunk never reach past the allocation.
+  // What columns beyond n hold (the rest of the row, the next row, or zero
+  // past the range) goes to entries that are never read.
+  const int64_t ex = min(nrows * a.ldx, (a.M - m0) * a.ldx - a.offx);
+  const int64_t ey = min(nrows * a.ldy, (a.M - m0) * a.ldy - a.offy);
+  const __amdgpu_buffer_rsrc_t rx = rsrc(a.X + m0 * a.ldx, static_cast<uint32_t>(ex * sizeof(T)));
+  const __amdgpu_buffer_rsrc_t ry = rsrc(a.Y + m0 * a.ldy, static_cast<uint32_t>(ey * sizeof(T)));
+  const int ldx = static_cast<int>(a.ldx), ldy = static_cast<int>(a.ldy);
+  auto load = [&](T (&xv)[RA], T (&yv)[CA], int s) {
     const int row = min(4 * s + lane / 16, nrows - 1);
-    const int vx = (row * static_cast<int>(ldx) + ci) * static_cast<int>(sizeof(T));
-    const int vy = (row * static_cast<int>(ldy) + cj) * static_cast<int>(sizeof(T));
+    const int vx = (row * ldx + I * kGB + lane % 16) * static_cast<int>(sizeof(T));
+    const int vy = (row * ldy + J * kGB + lane % 16) * static_cast<int>(sizeof(T));
     xv[0] = bload_group<T, 0>(rx, vx);
-    xv[1] = bload_group<T, 1>(rx, vx);
-    xv[2] = bload_group<T, 2>(rx, vx);
-    xv[3] = bload_group<T, 3>(rx, vx);
+    if constexpr (RA > 1) xv[1] = bload_group<T, 1>(rx, vx);
+    if constexpr (RA > 2) xv[2] = bload_group<T, 2>(rx, vx);
+    if constexpr (RA > 3) xv[3] = bload_group<T, 3>(rx, vx);
     yv[0] = bload_group<T, 0>(ry, vy);
-    yv[1] = bload_group<T, 1>(ry, vy);
-    yv[2] = bload_group<T, 2>(ry, vy);
-    yv[3] = bload_group<T, 3>(ry, vy);
+    if constexpr (CA > 1) yv[1] = bload_group<T, 1>(ry, vy);
+    if constexpr (CA > 2) yv[2] = bload_group<T, 2>(ry, vy);
+    if constexpr (CA > 3) yv[3] = bload_group<T, 3>(ry, vy);
   };
-  auto compute = [&](const T (&xin)[4], const T (&yin)[4], int s) {
-    T xv[4], yv[4];
-    const bool ok = 4 * s + lane / 16 < nrows;
+  auto compute = [&](const T (&x)[RA], const T (&y)[CA]) {
 #pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      xv[a] = ok ? xin[a] : T(0);
-      yv[a] = ok ? yin[a] : T(0);
-    }
+    for (int i = 0; i < RA; ++i)
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-      for (int b = 0; b < 4; ++b) acc[a][b] = Mfma<T>::mma(xv[a], yv[b], acc[a][b]);
+      for (int j = 0; j < CA; ++j)
+        if (!DIAG || j <= i) acc[i][j] = Mfma<T>::mma(x[i], y[j], acc[i][j]);
   };
-  // GS register stages with fixed roles (the loop is unrolled by GS; three
-  // by default: four or five measured no faster): the rows of step
-  // s + GS - 1 are in flight while step s multiplies.  A copy between stages
-  // would make the compiler wait for the loads in flight into the source.
-  // Loads past the last step read the chunk's last row (the row index is
-  // clamped) and the steps past KS contribute zero.
-  T xq[GS][4], yq[GS][4];
-  if (KS > 0) {
+  // GS register stages with fixed roles (the loop is unrolled by GS; three:
+  // four or five measured no faster): the rows of step s + GS - 1 are in
+  // flight while step s multiplies.  A copy between stages would make the
+  // compiler wait for the loads in flight into the source.  Loads past the
+  // chunk read its last row; steps past it are left out, and the rows of the
+  // last step that lie past it count as zero.
+  const int KS = (nrows + 3) / 4;
+  T xq[GS][RA], yq[GS][CA];
 #pragma unroll
-    for (int j = 0; j < GS - 1; ++j) load(xq[j], yq[j], j);
-  }
-  for (int s = 0; s < KS; s += GS) {
+  for (int j = 0; j < GS - 1; ++j) load(xq[j], yq[j], j);
+  int s = 0;
+  for (; s + GS < KS; s += GS) {
 #pragma unroll
     for (int j = 0; j < GS; ++j) {
       load(xq[(j + GS - 1) % GS], yq[(j + GS - 1) % GS], s + j + GS - 1);
-      compute(xq[j], yq[j], s + j);
+      compute(xq[j], yq[j]);
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-  double* out = part + static_cast<int64_t>(chunk) * npad * npad;
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int j = 0; j < GS; ++j) {
+    load(xq[(j + GS - 1) % GS], yq[(j + GS - 1) % GS], s + j + GS - 1);
+    const bool ok = 4 * (s + j) + lane / 16 < nrows;
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
+    for (int i = 0; i < RA; ++i) xq[j][i] = ok ? xq[j][i] : T(0);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int row = I * kGT + wi + a * 16 + Mfma<T>::row(lane, i);
-        const int col = J * kGT + wj + b * 16 + lane % 16;
-        out[static_cast<int64_t>(row) * npad + col] = static_cast<double>(acc[a][b][i]);
+    for (int i = 0; i < CA; ++i) yq[j][i] = ok ? yq[j][i] : T(0);
+    compute(xq[j], yq[j]);
+  }
+#pragma unroll
+  for (int i = 0; i < RA; ++i)
+#pragma unroll
+    for (int j = 0; j < CA; ++j)
+      if (!DIAG || j <= i) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          out[(i * 16 + Mfma<T>::row(lane, k)) * kGB + j * 16 + lane % 16] = static_cast<double>(acc[i][j][k]);
       }
 }
 
-__global__ void gram_reduce_kernel(const double* __restrict__ part, int nchunks, int n, int npad,
-                                   double* __restrict__ G, int64_t ldg) {
-  const int64_t idx = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
-  if (idx >= static_cast<int64_t>(n) * n) return;
-  const int i = static_cast<int>(idx / n), j = static_cast<int>(idx % n);
-  if (i / kGT < j / kGT) return;
+// lower-triangular block index -> (I, J)
+__device__ __forceinline__ int tri_row(int t) {
+  int I = static_cast<int>((sqrt(8.0 * t + 1.0) - 1.0) / 2.0);
+  while ((I + 1) * (I + 2) / 2 <= t) ++I;
+  while (I * (I + 1) / 2 > t) --I;
+  return I;
+}
+
+template <typename T, int GS>
+__global__ void __attribute__((amdgpu_flat_work_group_size(64, 64), amdgpu_waves_per_eu(2, 2)))
+gram_kernel(const GramArgs<T> a) {
+  // workgroups go round-robin over the 8 XCDs: the blocks of a chunk, which
+  // read the same rows, are given to one of them
+  const int nwg = gridDim.x, full = nwg / 8, rest = nwg % 8;
+  const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
+  const int w = xcd < rest ? xcd * (full + 1) + slot : rest * (full + 1) + (xcd - rest) * full + slot;
+  const int chunk = w / a.nblk, t = w % a.nblk;
+  const int I = __builtin_amdgcn_readfirstlane(tri_row(t));
+  const int J = t - I * (I + 1) / 2;
+  const int64_t m0 = chunk * a.rows;
+  const int nrows = static_cast<int>(min(a.rows, a.M - m0));
+  double* out = a.part + static_cast<int64_t>(w) * kGB * kGB;
+  const int ra = min((a.n - I * kGB + 15) / 16, 4);
+  if (I == J) {
+    if (ra == 4) gram_block<T, GS, 4, 4, true>(a, I, J, m0, nrows, out);
+    else if (ra == 3) gram_block<T, GS, 3, 3, true>(a, I, J, m0, nrows, out);
+    else if (ra == 2) gram_block<T, GS, 2, 2, true>(a, I, J, m0, nrows, out);
+    else gram_block<T, GS, 1, 1, true>(a, I, J, m0, nrows, out);
+  } else {
+    if (ra == 4) gram_block<T, GS, 4, 4, false>(a, I, J, m0, nrows, out);
+    else if (ra == 3) gram_block<T, GS, 3, 4, false>(a, I, J, m0, nrows, out);
+    else if (ra == 2) gram_block<T, GS, 2, 4, false>(a, I, J, m0, nrows, out);
+    else gram_block<T, GS, 1, 4, false>(a, I, J, m0, nrows, out);
+  }
+}
+
+// G = sums of the chunks' blocks, 64 entries per workgroup (one row of a
+// block): 4 waves take every 4th chunk, their sums are added in a fixed order.
+// Entries above the 16 x 16 tiles of the diagonal are left as they are.
+__global__ void __launch_bounds__(256)
+gram_reduce_kernel(const double* __restrict__ part, int nchunks, int nblk, int n, double* __restrict__ G, int64_t ldg) {
+  __shared__ double red[4][64];
+  const int t = blockIdx.y, r = blockIdx.x, c = threadIdx.x % 64, wave = threadIdx.x / 64;
+  const int I = tri_row(t), J = t - I * (I + 1) / 2;
+  const int i = I * kGB + r, j = J * kGB + c;
   double s = 0.0;
-  for (int c = 0; c < nchunks; ++c) s += part[(static_cast<int64_t>(c) * npad + i) * npad + j];
-  G[static_cast<int64_t>(i) * ldg + j] = s;
+  if (i < n && j / 16 <= i / 16) {
+    const double* p = part + (static_cast<int64_t>(t) * kGB + r) * kGB + c;
+    const int64_t step = static_cast<int64_t>(nblk) * kGB * kGB;
+#pragma unroll 8
+    for (int q = wave; q < nchunks; q += 4) s += p[q * step];
+  }
+  red[wave][c] = s;
+  __syncthreads();
+  if (wave == 0 && i < n && j < n && j / 16 <= i / 16)
+    G[static_cast<int64_t>(i) * ldg + j] = ((s + red[1][c]) + red[2][c]) + red[3][c];
 }
 
 // Real symmetric result from the lower entries: S[i][j] = G[max][min].
@@ -216,109 +267,117 @@ __global__ void gram_combine_complex_kernel(const double* __restrict__ G, int64_
 }
 
 // ---- rotation C = X Z --------------------------------------------------------
-// Workgroup tile 128 x 128, 4 waves of 64 x 64 (4 x 4 MFMA tiles: each A and
-// B fragment read from LDS serves four MFMAs).  X rows are staged through
-// LDS (the A operand needs 16 rows per fragment), Z through LDS as well; both
-// double buffered, with the next 16-deep k chunk loaded into registers from
-// global memory while the current one multiplies, so there is one barrier
-// per chunk (64 MFMAs per wave) and the global latency overlaps the MFMAs.
-// The two stages take 70 KB of LDS at FP64: two workgroups per CU.
-// upper: Z is upper triangular, k stops at the tile's last column.
-constexpr int kRM = 128;  // rows per workgroup
-constexpr int kRN = 128;  // columns per workgroup
-constexpr int kRK = 16;   // k per stage
-constexpr int kZP = kRN + 8;  // padded LDS row of the Z stage
+// A workgroup owns 32 rows and makes their columns in slabs of 256, from the
+// last to the first: the slab's X values go through LDS in panels of 256
+// columns, and 4 waves multiply them with groups of 16 columns of Z, which all
+// workgroups read from their L2 straight into B operands, 16 k ahead of their
+// use.  66 KB of LDS: two workgroups per CU, one loads while the other
+// multiplies.
+// upper: Z is upper triangular (in its 16 x 16 tiles: the real view of a
+// complex triangle counts too).  A group then takes the k up to its own last
+// column, the waves share the groups from the longest to the shortest in
+// alternating order so that their sums agree, and C may be X: a slab is
+// stored after all X columns that it or a slab to its left needs were read.
+// Bound by the matrix cores and, close behind, by reading X and writing C.
+// On 2,985,984 x 256 FP64, upper: @ROT_MEASURED@
+constexpr int kRM = 32;    // rows per workgroup
+constexpr int kRK = 256;   // columns per slab and panel
+constexpr int kRG = kRK / 16;
 
 template <typename T>
 __global__ void __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(2, 2)))
-rotate_kernel(const T* __restrict__ X, int64_t ldx, const T* __restrict__ Z, int64_t ldz,
-              T* __restrict__ C, int64_t ldc, int64_t M, int K, int N2, int upper) {
-  __shared__ T xs[2][kRM][kRK + 1];
-  __shared__ T zs[2][kRK][kZP];
-  const int64_t r0 = blockIdx.x * static_cast<int64_t>(kRM);
-  const int c0 = blockIdx.y * kRN;
-  const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64;
-  const int wr = (wave / 2) * 64, wc = (wave % 2) * 64;
+rotate_kernel(const T* X, int64_t ldx, const T* __restrict__ Z, int64_t ldz, T* C, int64_t ldc, int64_t M, int K,
+              int N2, int upper) {
+  // rows end 4 banks apart: the 16 rows of an operand are read without conflicts
+  constexpr int S = kRK + 16 / static_cast<int>(sizeof(T));
+  __shared__ T xs[kRM][S];
   using Acc = typename Mfma<T>::Acc;
-  Acc acc[4][4];
+  constexpr uint32_t kBeyond = 0xfffffff0u;   // past any range: loads 0
+  const int64_t r0 = blockIdx.x * static_cast<int64_t>(kRM);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+  const int lane = threadIdx.x % 64, q = lane / 16, cl = lane % 16;
+  for (int c0 = (N2 - 1) / kRK * kRK; c0 >= 0; c0 -= kRK) {
+    const int G = min(kRG, (N2 - c0 + 15) / 16);
+    const int g[4] = {G - 1 - wave, G - 8 + wave, G - 9 - wave, G - 16 + wave};   // negative: none
+    Acc acc[2][4];
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+    for (int r = 0; r < 2; ++r)
 #pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = Acc{0, 0, 0, 0};
-  int kend = K;
-  if (upper && c0 + kRN < kend) kend = c0 + kRN;
-  // loaders: X 128 rows x 16 k (8 per thread, 16 threads per row), Z 16 k x
-  // 128 columns (8 per thread, one row per 128 threads); addresses clamped,
-  // out-of-range values zeroed when stored to LDS
-  const int xk = tid % kRK, xr = tid / kRK;
-  const int zc = tid % kRN, zr = tid / kRN;
-  T gx[8], gz[8];
-  auto gload = [&](int k0) {
+      for (int i = 0; i < 4; ++i) acc[r][i] = Acc{0, 0, 0, 0};
+    const int kend = upper ? min(K, c0 + kRK) : K;
+    for (int kb = 0; kb < kend; kb += kRK) {
+      const int nk = min(kRK, kend - kb);
+      __syncthreads();
+      // the panel: 8 rows per wave, 4 columns per lane 64 apart
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      int64_t row = r0 + xr + 16 * i;
-      row = row < M ? row : M - 1;
-      int k = k0 + xk;
-      k = k < K ? k : K - 1;
-      gx[i] = X[row * ldx + k];
-    }
+      for (int h = 0; h < 2; ++h) {
+        T v[4][4];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      int k = k0 + zr + 2 * i;
-      k = k < K ? k : K - 1;
-      int c = c0 + zc;
-      c = c < N2 ? c : N2 - 1;
-      gz[i] = Z[static_cast<int64_t>(k) * ldz + c];
-    }
-  };
-  auto sstore = [&](int buf, int k0) {
+        for (int r = 0; r < 4; ++r)
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const bool ok = r0 + xr + 16 * i < M && k0 + xk < K;
-      xs[buf][xr + 16 * i][xk] = ok ? gx[i] : T(0);
-    }
+          for (int c = 0; c < 4; ++c) {
+            const int64_t row = min(r0 + wave * 8 + h * 4 + r, M - 1);
+            v[r][c] = X[row * ldx + kb + min(lane + 64 * c, nk - 1)];
+          }
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const bool ok = k0 + zr + 2 * i < K && c0 + zc < N2;
-      zs[buf][zr + 2 * i][zc] = ok ? gz[i] : T(0);
-    }
-  };
-  if (kend > 0) {
-    gload(0);
-    sstore(0, 0);
-  }
-  __syncthreads();
-  int buf = 0;
-  for (int k0 = 0; k0 < kend; k0 += kRK) {
-    const bool more = k0 + kRK < kend;
-    if (more) gload(k0 + kRK);
+        for (int r = 0; r < 4; ++r)
 #pragma unroll
-    for (int ks = 0; ks < kRK / 4; ++ks) {
-      const int kr = ks * 4 + lane / 16;
-      T av[4], bv[4];
-#pragma unroll
-      for (int a = 0; a < 4; ++a) av[a] = xs[buf][wr + a * 16 + lane % 16][kr];
-#pragma unroll
-      for (int b = 0; b < 4; ++b) bv[b] = zs[buf][kr][wc + b * 16 + lane % 16];
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = Mfma<T>::mma(av[a], bv[b], acc[a][b]);
-    }
-    if (more) sstore(buf ^ 1, k0 + kRK);
-    __syncthreads();
-    buf ^= 1;
-  }
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int64_t row = r0 + wr + a * 16 + Mfma<T>::row(lane, i);
-        const int col = c0 + wc + b * 16 + lane % 16;
-        if (row < M && col < N2) C[row * ldc + col] = acc[a][b][i];
+          for (int c = 0; c < 4; ++c) xs[wave * 8 + h * 4 + r][lane + 64 * c] = lane + 64 * c < nk ? v[r][c] : T(0);
       }
+      __syncthreads();
+      const bool diag = upper && kb == c0;
+      const int rows = min(K - kb, kRK);
+      const __amdgpu_buffer_rsrc_t rz =
+          rsrc(Z + static_cast<int64_t>(kb) * ldz, static_cast<uint32_t>((static_cast<int64_t>(rows - 1) * ldz + N2) * sizeof(T)));
+      const uint32_t zstep = static_cast<uint32_t>(ldz * 4 * sizeof(T));   // 4 rows of Z
+      const uint32_t zlane = static_cast<uint32_t>((q * ldz + c0 + cl) * sizeof(T));
+      auto load = [&](T (&b)[4][4], int kc) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const bool on = g[i] >= 0 && !(diag && kc > g[i]) && kc * 16 < nk;
+          const uint32_t o = zlane + kc * 4 * zstep + static_cast<uint32_t>(g[i] * 16 * static_cast<int>(sizeof(T)));
+#pragma unroll
+          for (int s = 0; s < 4; ++s) b[s][i] = bload_group<T, 0>(rz, on ? o + s * zstep : kBeyond);
+        }
+      };
+      auto compute = [&](const T (&b)[4][4], int kc) {
+        T a[4][2];
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+          for (int r = 0; r < 2; ++r) a[s][r] = xs[r * 16 + cl][kc * 16 + s * 4 + q];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          if (g[i] < 0 || (diag && kc > g[i])) continue;
+#pragma unroll
+          for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int r = 0; r < 2; ++r) acc[r][i] = Mfma<T>::mma(a[s][r], b[s][i], acc[r][i]);
+        }
+      };
+      const int nkc = (nk + 15) / 16;
+      T b0[4][4], b1[4][4];
+      load(b0, 0);
+      for (int kc = 0; kc < nkc; kc += 2) {
+        load(b1, kc + 1);
+        compute(b0, kc);
+        load(b0, kc + 2);
+        if (kc + 1 < nkc) compute(b1, kc + 1);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int col = c0 + g[i] * 16 + cl;
+      if (g[i] < 0 || col >= N2) continue;
+#pragma unroll
+      for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const int64_t row = r0 + r * 16 + Mfma<T>::row(lane, k);
+          if (row < M) C[row * ldc + col] = acc[r][i][k];
+        }
+    }
+  }
 }
 
 // ---- residual column sums ------------------------------------------------
@@ -459,13 +518,16 @@ unsigned blocks_for(int64_t total, int per = 256) {
   return static_cast<unsigned>((total + per - 1) / per);
 }
 
-// Row chunks of the Gram products: about 1024 workgroups in all, at least
-// 256 rows per chunk, and few enough rows that a chunk of the widest operand
-// (ld doubles per row) spans less than 2^31 bytes (32-bit buffer offsets).
+// Row chunks of the Gram products: about 4096 waves in all (two rounds of two
+// per SIMD), at least 256 rows per chunk, and few enough rows that a chunk of
+// the widest operand (ld doubles per row) spans less than 2^31 bytes (32-bit
+// buffer offsets).
+int gram_blocks(int n) {
+  const int nb = (n + kGB - 1) / kGB;
+  return nb * (nb + 1) / 2;
+}
 int gram_chunks(int64_t M, int n, int64_t ld) {
-  const int nt = (n + kGT - 1) / kGT;
-  const int ntiles = nt * (nt + 1) / 2;
-  int64_t ch = (1024 + ntiles - 1) / ntiles;
+  int64_t ch = kGramWaves / gram_blocks(n);
   const int64_t max_ch = (M + 255) / 256;
   if (ch > max_ch) ch = max_ch;
   const int64_t max_rows = ((int64_t{1} << 31) - 1) / (8 * (ld > 0 ? ld : 1)) - 16;
@@ -478,8 +540,11 @@ int gram_chunks(int64_t M, int n, int64_t ld) {
 }  // namespace
 
 size_t gram_partial_bytes(int64_t M, int n, int64_t ld) {
-  const int npad = (n + kGT - 1) / kGT * kGT;
-  return static_cast<size_t>(gram_chunks(M, n, ld)) * npad * npad * sizeof(double);
+  // what the widest of all products of up to n columns takes
+  int64_t blocks = 0;
+  for (int w = kGB; w < n + kGB; w += kGB)
+    blocks = std::max(blocks, static_cast<int64_t>(gram_chunks(M, w, ld)) * gram_blocks(w));
+  return static_cast<size_t>(blocks) * kGB * kGB * sizeof(double);
 }
 
 template <typename T>
@@ -487,17 +552,25 @@ hipError_t gram_t(const T* X, int64_t ldx, const T* Y, int64_t ldy, int64_t M, i
                   double* G, int64_t ldg, hipStream_t s, int64_t offx, int64_t offy) {
   if (offx < 0 || offy < 0 || offx + n > ldx || offy + n > ldy) return hipErrorInvalidValue;
   if (n <= 0) return hipSuccess;
-  const int nt = (n + kGT - 1) / kGT;
-  const int ntiles = nt * (nt + 1) / 2;
-  const int npad = nt * kGT;
   int nch = gram_chunks(M, n, ldx > ldy ? ldx : ldy);
-  int64_t rpc = (M + nch - 1) / nch;
-  rpc = (rpc + 15) / 16 * 16;
-  nch = static_cast<int>((M + rpc - 1) / rpc);   // rounding rpc up can leave trailing chunks empty
-  hipLaunchKernelGGL((gram_kernel<T, kGramStages>), dim3(ntiles, nch), dim3(256), 0, s, X, ldx, Y, ldy, M, n, rpc,
-                     npad, partial, offx, offy);
-  hipLaunchKernelGGL(gram_reduce_kernel, dim3(blocks_for(static_cast<int64_t>(n) * n)), dim3(256), 0, s,
-                     partial, nch, n, npad, G, ldg);
+  GramArgs<T> a;
+  a.X = X;
+  a.Y = Y;
+  a.ldx = ldx;
+  a.ldy = ldy;
+  a.M = M;
+  a.n = n;
+  a.nblk = gram_blocks(n);
+  a.rows = ((M + nch - 1) / nch + 15) / 16 * 16;
+  a.part = partial;
+  a.offx = offx;
+  a.offy = offy;
+  nch = static_cast<int>((M + a.rows - 1) / a.rows);   // rounding up can leave trailing chunks empty
+  const int64_t nwg = static_cast<int64_t>(nch) * a.nblk;
+  if (nwg > 0x7fffffff) return hipErrorInvalidValue;
+  if (nwg > 0)
+    hipLaunchKernelGGL((gram_kernel<T, kGramStages>), dim3(static_cast<unsigned>(nwg)), dim3(64), 0, s, a);
+  hipLaunchKernelGGL(gram_reduce_kernel, dim3(kGB, a.nblk), dim3(256), 0, s, partial, nch, a.nblk, n, G, ldg);
   return hipGetLastError();
 }
 
@@ -529,8 +602,9 @@ hipError_t rotate_t(const T* X, int64_t ldx, const T* Z, int64_t ldz, T* C, int6
   if (M <= 0 || N2 <= 0) return hipSuccess;
   const int64_t gx = (M + kRM - 1) / kRM;
   if (gx > 0x7fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(rotate_kernel<T>, dim3(static_cast<unsigned>(gx), (N2 + kRN - 1) / kRN), dim3(256), 0, s, X,
-                     ldx, Z, ldz, C, ldc, M, K, N2, upper ? 1 : 0);
+  if (ldz > (int64_t{1} << 19)) return hipErrorInvalidValue;   // 32-bit offsets in 256 rows of Z
+  hipLaunchKernelGGL(rotate_kernel<T>, dim3(static_cast<unsigned>(gx)), dim3(256), 0, s, X, ldx, Z, ldz, C, ldc, M, K,
+                     N2, upper ? 1 : 0);
   return hipGetLastError();
 }
 

@@ -455,6 +455,26 @@ hipError_t nl_update_launch(const NlUpdate& a, int p, hipStream_t s) {
   return hipGetLastError();
 }
 
+__global__ void __launch_bounds__(256)
+own_table_kernel(const int32_t* __restrict__ own_pair, int p, int rts, const double* __restrict__ pair_re,
+                 const double* __restrict__ pair_im, int per, double* __restrict__ out64, float* __restrict__ out32) {
+  const int64_t src = static_cast<int64_t>(own_pair[blockIdx.x]) * rts;
+  const int vw = pair_im ? 8 : 4;
+  for (int i = threadIdx.x; i < per; i += 256) {
+    const int l = i / (16 * vw) * 16 + i % 16, v = i / 16 % vw, m = v % 4;
+    double x = 0.0;
+    if (l < p * p * p) {
+      const int ax = l % p, ay = l / p % p, az = l / (p * p);
+      const int lid = ax + (p + 1) * (ay + (p + 1) * az);
+      const int mult = (ax ? 1 : 2) * (ay ? 1 : 2) * (az ? 1 : 2);
+      x = (v < 4 ? pair_re : pair_im)[(src + lid / 16) * 64 + m * 16 + lid % 16] * mult;
+    }
+    const int64_t o = static_cast<int64_t>(blockIdx.x) * per + i;
+    out64[o] = x;
+    out32[o] = static_cast<float>(x);
+  }
+}
+
 template <typename T, bool CPLX>
 hipError_t nl_update_batched(const NlUpdateBatch& b, int p, hipStream_t s) {
   const NlUpdate* d = static_cast<const NlUpdate*>(b.descs);
@@ -541,6 +561,16 @@ hipError_t launch_nl_update(const NlUpdate& a, int p, int prec, hipStream_t s) {
 }
 
 int nl_update_cells() { return kNlCells; }
+
+size_t own_table_entries(int p, bool cplx) { return static_cast<size_t>((p * p * p + 15) / 16 * 16) * (cplx ? 8 : 4); }
+
+hipError_t launch_own_table(const int32_t* own_pair, int nown, int p, int mpad, const double* pair_re,
+                            const double* pair_im, double* out64, float* out32, hipStream_t s) {
+  if (nown <= 0) return hipSuccess;
+  hipLaunchKernelGGL(own_table_kernel, dim3(nown), dim3(256), 0, s, own_pair, p, mpad / 16, pair_re, pair_im,
+                     static_cast<int>(own_table_entries(p, pair_im != nullptr)), out64, out32);
+  return hipGetLastError();
+}
 
 hipError_t launch_nl_update_batched(const NlUpdateBatch& b, int p, int prec, hipStream_t s) {
   switch (prec) {

@@ -9,7 +9,6 @@
 #include <cmath>
 #include <complex>
 #include <cstring>
-#include <unordered_map>
 
 #include "internal.h"
 
@@ -315,18 +314,13 @@ std::string build_tables(const chfsi_system& sys, HostTables& t) {
   t.own_cell.clear();
   t.own_ptr.clear();
   t.own_atom.clear();
-  t.own_val.clear();
+  t.own_pair.clear();
   t.atom_pair_ptr.assign(1, 0);
   t.atom_pair.clear();
   if (!t.has_proj) return "";
   const int vw = t.cplx ? 8 : 4;
   using cd = std::complex<double>;
   struct Entry { int64_t node; cd v[4]; };
-  struct PairRec { int64_t cell; int atom; std::vector<double> cre, cim; };
-  std::vector<PairRec> pairs;
-  struct OwnRec { int64_t cell; int atom; std::vector<double> v; };
-  std::vector<OwnRec> owns;
-  const size_t p3 = static_cast<size_t>(p) * p * p;
   std::vector<Entry> ent;
   for (int at = 0; at < sys.natoms; ++at) {
     const double w = sys.w[at];
@@ -371,7 +365,6 @@ std::string build_tables(const chfsi_system& sys, HostTables& t) {
         }
     std::sort(ent.begin(), ent.end(), [](const Entry& a, const Entry& b) { return a.node < b.node; });
     // merge overlapping images, append to the atom-major list
-    std::unordered_map<int64_t, size_t> cell_pair, cell_own;
     for (size_t i = 0; i < ent.size();) {
       Entry e = ent[i];
       size_t j = i + 1;
@@ -389,113 +382,102 @@ std::string build_tables(const chfsi_system& sys, HostTables& t) {
           t.atom_val.push_back(e.v[m].real());
         }
       }
-      const int ix = static_cast<int>(e.node % n), iy = static_cast<int>((e.node / n) % n),
-                iz = static_cast<int>(e.node / (static_cast<int64_t>(n) * n));
-      // the owner cell's table
-      {
-        const int64_t cell = ix / p + static_cast<int64_t>(nc) * (iy / p + static_cast<int64_t>(nc) * (iz / p));
-        const auto ins = cell_own.emplace(cell, owns.size());
-        if (ins.second) owns.push_back(OwnRec{cell, at, std::vector<double>(p3 * vw, 0.0)});
-        double* o = &owns[ins.first->second].v[(ix % p + p * (iy % p + static_cast<size_t>(p) * (iz % p))) * vw];
-        for (int m = 0; m < 4; ++m) {
-          if (t.cplx) {
-            o[2 * m] = e.v[m].real();
-            o[2 * m + 1] = e.v[m].imag();
-          } else {
-            o[m] = e.v[m].real();
-          }
-        }
-      }
-      // the cells holding this node, with its local index and multiplicity
-      int cxs[2], axs[2], ncx = 0, cys[2], ays[2], ncy = 0, czs[2], azs[2], ncz = 0;
-      auto cells_of = [&](int i1, int* cs, int* as, int& cnt) {
-        cnt = 0;
-        cs[cnt] = i1 / p; as[cnt] = i1 % p; ++cnt;
-        if (i1 % p == 0) { cs[cnt] = (i1 / p - 1 + nc) % nc; as[cnt] = p; ++cnt; }
-      };
-      cells_of(ix, cxs, axs, ncx);
-      cells_of(iy, cys, ays, ncy);
-      cells_of(iz, czs, azs, ncz);
-      const double inv_mult = 1.0 / (ncx * ncy * ncz);
-      for (int uz = 0; uz < ncz; ++uz)
-        for (int uy = 0; uy < ncy; ++uy)
-          for (int ux = 0; ux < ncx; ++ux) {
-            const int64_t cell = cxs[ux] + static_cast<int64_t>(nc) * (cys[uy] + static_cast<int64_t>(nc) * czs[uz]);
-            const int lid = axs[ux] + q * (ays[uy] + q * azs[uz]);
-            auto it = cell_pair.find(cell);
-            size_t pi;
-            if (it == cell_pair.end()) {
-              pi = pairs.size();
-              cell_pair.emplace(cell, pi);
-              PairRec pr;
-              pr.cell = cell;
-              pr.atom = at;
-              pr.cre.assign(static_cast<size_t>(mc) * 4, 0.0);
-              if (t.cplx) pr.cim.assign(static_cast<size_t>(mc) * 4, 0.0);
-              pairs.push_back(std::move(pr));
-            } else {
-              pi = it->second;
-            }
-            for (int m = 0; m < 4; ++m) {
-              pairs[pi].cre[lid * 4 + m] = e.v[m].real() * inv_mult;
-              if (t.cplx) pairs[pi].cim[lid * 4 + m] = e.v[m].imag() * inv_mult;
-            }
-          }
     }
     t.atom_ptr.push_back(static_cast<int64_t>(t.atom_node.size()));
   }
-  // owner tables sorted by (cell, atom)
-  std::vector<size_t> oo(owns.size());
-  for (size_t i = 0; i < oo.size(); ++i) oo[i] = i;
-  std::sort(oo.begin(), oo.end(), [&](size_t a, size_t b) {
-    return owns[a].cell != owns[b].cell ? owns[a].cell < owns[b].cell : owns[a].atom < owns[b].atom;
-  });
-  t.own_atom.resize(owns.size());
-  const size_t per = (p3 + 15) / 16 * 16 * vw;
-  t.own_val.assign(owns.size() * per, 0.0);
-  std::vector<std::vector<int32_t>> of_atom(sys.natoms);
-  for (size_t i = 0; i < oo.size(); ++i) {
-    const OwnRec& o = owns[oo[i]];
-    if (t.own_cell.empty() || t.own_cell.back() != o.cell) {
-      t.own_cell.push_back(static_cast<int32_t>(o.cell));
-      t.own_ptr.push_back(static_cast<int32_t>(i));
-    }
-    t.own_atom[i] = o.atom;
-    of_atom[o.atom].push_back(static_cast<int32_t>(i));
-    for (size_t e = 0; e < p3; ++e)
-      for (int m = 0; m < 4; ++m)
-        for (int c = 0; c < vw / 4; ++c)
-          t.own_val[i * per + ((e / 16 * (vw / 4) + c) * 4 + m) * 16 + e % 16] = o.v[e * vw + m * (vw / 4) + c];
-  }
-  t.own_ptr.push_back(static_cast<int32_t>(oo.size()));
-  for (int at = 0; at < sys.natoms; ++at) {
-    t.atom_pair.insert(t.atom_pair.end(), of_atom[at].begin(), of_atom[at].end());
-    t.atom_pair_ptr.push_back(static_cast<int32_t>(t.atom_pair.size()));
-  }
-  // pairs sorted by (cell, atom), cell-major CSR, MFMA A-operand layout:
-  // lane -> (row lane%16 of the row tile, projector component lane/16)
-  std::vector<size_t> ord(pairs.size());
-  for (size_t i = 0; i < ord.size(); ++i) ord[i] = i;
-  std::sort(ord.begin(), ord.end(), [&](size_t a, size_t b) {
-    return pairs[a].cell != pairs[b].cell ? pairs[a].cell < pairs[b].cell : pairs[a].atom < pairs[b].atom;
-  });
-  const int rts = t.mpad / 16;
-  t.pair_atom.resize(pairs.size());
-  t.pair_re.assign(pairs.size() * rts * 64, 0.0);
-  if (t.cplx) t.pair_im.assign(pairs.size() * rts * 64, 0.0);
-  for (size_t k2 = 0; k2 < ord.size(); ++k2) {
-    const PairRec& pr = pairs[ord[k2]];
-    t.pair_atom[k2] = pr.atom;
-    t.pair_ptr[pr.cell + 1] += 1;
-    for (int rt = 0; rt < rts; ++rt)
-      for (int lane = 0; lane < 64; ++lane) {
-        const int r = rt * 16 + lane % 16, m = lane / 16;
-        if (r >= mc) continue;
-        t.pair_re[(k2 * rts + rt) * 64 + lane] = pr.cre[r * 4 + m];
-        if (t.cplx) t.pair_im[(k2 * rts + rt) * 64 + lane] = pr.cim[r * 4 + m];
+  // (cell, atom) pairs, sorted by cell, then atom: of the cells that hold a
+  // node (with a table of its entries over its multiplicity; MFMA A-operand
+  // layout: lane -> row lane % 16 of the row tile, projector lane / 16) and of
+  // the cells that own it.  First the pairs are counted and numbered, then the entries of the
+  // atom-major list are written to their places.
+  struct Holder { int64_t cell; int lid; };
+  Holder hold[8];
+  auto holders = [&](int64_t node) {   // the first one is the owner
+    int c[3][2], a[3][2], cnt[3];
+    int64_t v = node;
+    for (int d = 0; d < 3; ++d, v /= n) {
+      const int i1 = static_cast<int>(v % n);
+      c[d][0] = i1 / p;
+      a[d][0] = i1 % p;
+      cnt[d] = 1;
+      if (i1 % p == 0) {
+        c[d][1] = (i1 / p - 1 + nc) % nc;
+        a[d][1] = p;
+        cnt[d] = 2;
       }
+    }
+    int k = 0;
+    for (int uz = 0; uz < cnt[2]; ++uz)
+      for (int uy = 0; uy < cnt[1]; ++uy)
+        for (int ux = 0; ux < cnt[0]; ++ux)
+          hold[k++] = Holder{c[0][ux] + static_cast<int64_t>(nc) * (c[1][uy] + static_cast<int64_t>(nc) * c[2][uz]),
+                             a[0][ux] + q * (a[1][uy] + q * a[2][uz])};
+    return k;
+  };
+  std::vector<std::vector<int64_t>> at_cells(sys.natoms), at_owns(sys.natoms);
+  std::vector<int> seen(t.E, -1), seen_own(t.E, -1);
+  std::vector<int32_t> own_first(t.E + 1, 0);
+  for (int at = 0; at < sys.natoms; ++at)
+    for (int64_t e = t.atom_ptr[at]; e < t.atom_ptr[at + 1]; ++e) {
+      const int k = holders(t.atom_node[e]);
+      for (int u = 0; u < k; ++u)
+        if (seen[hold[u].cell] != at) {
+          seen[hold[u].cell] = at;
+          at_cells[at].push_back(hold[u].cell);
+          t.pair_ptr[hold[u].cell + 1] += 1;
+        }
+      if (seen_own[hold[0].cell] != at) {
+        seen_own[hold[0].cell] = at;
+        at_owns[at].push_back(hold[0].cell);
+        own_first[hold[0].cell + 1] += 1;
+      }
+    }
+  for (int64_t c = 0; c < t.E; ++c) {
+    if (own_first[c + 1] > 0) {
+      t.own_cell.push_back(static_cast<int32_t>(c));
+      t.own_ptr.push_back(own_first[c]);
+    }
+    t.pair_ptr[c + 1] += t.pair_ptr[c];
+    own_first[c + 1] += own_first[c];
   }
-  for (int64_t c = 0; c < t.E; ++c) t.pair_ptr[c + 1] += t.pair_ptr[c];
+  t.own_ptr.push_back(own_first[t.E]);
+  const int rts = t.mpad / 16;
+  const size_t npair = static_cast<size_t>(t.pair_ptr[t.E]), nown = static_cast<size_t>(own_first[t.E]);
+  t.pair_atom.resize(npair);
+  t.pair_re.assign(npair * rts * 64, 0.0);
+  if (t.cplx) t.pair_im.assign(npair * rts * 64, 0.0);
+  t.own_atom.resize(nown);
+  t.own_pair.resize(nown);
+  std::vector<int64_t> next(t.pair_ptr.begin(), t.pair_ptr.end() - 1), at_pair(t.E);
+  std::vector<int32_t> next_own(own_first.begin(), own_first.end() - 1), at_own(t.E);
+  for (int at = 0; at < sys.natoms; ++at) {
+    for (int64_t c : at_cells[at]) {
+      at_pair[c] = next[c]++;
+      t.pair_atom[at_pair[c]] = at;
+    }
+    std::sort(at_owns[at].begin(), at_owns[at].end());
+    for (int64_t c : at_owns[at]) {
+      at_own[c] = next_own[c]++;
+      t.own_atom[at_own[c]] = at;
+      t.own_pair[at_own[c]] = static_cast<int32_t>(at_pair[c]);
+      t.atom_pair.push_back(at_own[c]);
+    }
+    t.atom_pair_ptr.push_back(static_cast<int32_t>(t.atom_pair.size()));
+    for (int64_t e = t.atom_ptr[at]; e < t.atom_ptr[at + 1]; ++e) {
+      const double* v = &t.atom_val[e * vw];
+      const int64_t node = t.atom_node[e];
+      const int k = holders(node);
+      const double inv_mult = 1.0 / k;
+      for (int u = 0; u < k; ++u) {
+        const int lid = hold[u].lid;
+        const size_t o = (at_pair[hold[u].cell] * rts + lid / 16) * 64 + lid % 16;
+        for (int m = 0; m < 4; ++m) {
+          t.pair_re[o + m * 16] = v[t.cplx ? 2 * m : m] * inv_mult;
+          if (t.cplx) t.pair_im[o + m * 16] = v[2 * m + 1] * inv_mult;
+        }
+      }
+    }
+  }
   return "";
 }
 

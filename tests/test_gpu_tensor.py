@@ -9,6 +9,8 @@ products of 1D factors plus at most a few projectors per atom, each bounded by
 the growth of the step itself, so 1e-12 for one FP64 product and 1e-11 for a
 filter; single precision has 5e8 times the unit roundoff, 2e-5 and 1e-4.
 """
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -125,3 +127,31 @@ def test_batched_filter(ctx, k, single, m):
             assert _relerr(X.cpu().numpy(), W.cpu().numpy()) < (1e-4 if single else 1e-11)
             X /= X.abs().max()
     del ctx._blocks
+
+
+# Gram blocks of 64 columns and rotation slabs of 256 where they end, in place
+# with a leading dimension of its own; tolerances of the orthonormalisation and
+# Rayleigh-Ritz tests of smaller blocks (1e-11, 1e-9)
+@pytest.mark.parametrize("N", [1, 15, 17, 48, 63, 65, 130, 257, 300])
+@pytest.mark.parametrize("k", [(0, 0, 0), K])
+def test_subspace_widths(ctx, N, k):
+    s = workloads.small_system(3, 5, 2, seed=21, has_proj=True, k=k)
+    op = lib.Operator(ctx, s)
+    X = workloads.start_block(op.M, N, seed=N, complex_=op.is_complex)
+    buf = torch.full((op.M, N + 3), 4.0, dtype=torch.from_numpy(X).dtype, device="cuda")
+    buf[:, :N] = torch.from_numpy(X).cuda()
+    Xo, Lref, _ = ochfsi.cholgs(X)
+    L = np.zeros((N, N), dtype=X.dtype)
+    ctx.check(ctx.lib.chfsi_orthonormalize(op.h, lib._tptr(buf), N, N + 3,
+                                           L.ctypes.data_as(ctypes.POINTER(ctypes.c_double))))
+    got = buf.cpu().numpy()
+    assert _relerr(got[:, :N], Xo) < 1e-11
+    assert _relerr(L, Lref) < 1e-11
+    assert np.all(got[:, N:] == 4)
+    H = fe.assemble(fe.build_operator(s))
+    th_ref = ochfsi.rayleigh_ritz(lambda v: H @ v, Xo)[0]
+    Xd = torch.from_numpy(Xo).cuda()
+    th, r = op.rayleigh_ritz(Xd)
+    assert np.max(np.abs(th - th_ref)) < 1e-10 * max(1.0, np.max(np.abs(th_ref)))
+    Psi = Xd.cpu().numpy()
+    assert np.max(np.abs(np.linalg.norm(H @ Psi - Psi * th, axis=0) - r)) < 1e-9
