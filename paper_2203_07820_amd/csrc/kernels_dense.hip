@@ -57,12 +57,10 @@ template <> struct Mfma<float> {
 // 16 x 16 tiles.  The blocks then differ in work; as single-wave workgroups,
 // in two rounds over the device, they level out.  On 2,985,984 x 256 FP64
 // (136 of the 192 tiles that 128 x 128 workgroups multiplied):
-// @GRAM_MEASURED@
+// 5.9 -> 4.3 ms, 77 % of the cycles multiplying; on 216,000 x 160, 0.384 ->
+// 0.166 ms.  (2048 waves: 0.177 ms there; 8192: 0.170 ms and a longer sum.)
 constexpr int kGB = 64;          // columns of a block
-#ifndef VGW
-#define VGW 4096
-#endif
-constexpr int kGramWaves = VGW;
+constexpr int kGramWaves = 4096;  // waves of a product: two rounds of two per SIMD
 constexpr int kGramStages = 3;   // register stages (loads GS - 1 steps ahead)
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* p, uint32_t bytes) {
@@ -270,7 +268,7 @@ __global__ void gram_combine_complex_kernel(const double* __restrict__ G, int64_
 // A workgroup owns 32 rows and makes their columns in slabs of 256, from the
 // last to the first: the slab's X values go through LDS in panels of 256
 // columns, and 4 waves multiply them with groups of 16 columns of Z, which all
-// workgroups read from their L2 straight into B operands, 16 k ahead of their
+// workgroups read from their L2 straight into B operands, 32 k ahead of their
 // use.  66 KB of LDS: two workgroups per CU, one loads while the other
 // multiplies.
 // upper: Z is upper triangular (in its 16 x 16 tiles: the real view of a
@@ -278,11 +276,16 @@ __global__ void gram_combine_complex_kernel(const double* __restrict__ G, int64_
 // column, the waves share the groups from the longest to the shortest in
 // alternating order so that their sums agree, and C may be X: a slab is
 // stored after all X columns that it or a slab to its left needs were read.
-// Bound by the matrix cores and, close behind, by reading X and writing C.
-// On 2,985,984 x 256 FP64, upper: @ROT_MEASURED@
+// Bound by the matrix cores (56 % of the cycles multiply) and by Z's way from
+// the L2; reading X and writing C take half the time.  On 2,985,984 x 256 FP64,
+// upper, the products of whole 128 x 128 tiles into a second block took 6.45 ms
+// and the copy back 2.7 ms; this takes 5.45 ms.  216,000 x 160: 0.281 -> 0.182
+// ms.  (4 or 8 units in flight: 5.47 and 5.90 ms; the next panel fetched during
+// the multiplications by workgroups that stay for 8 row blocks: 5.6 ms; 64 rows
+// by 8 waves: 5.9 ms.)
 constexpr int kRM = 32;    // rows per workgroup
 constexpr int kRK = 256;   // columns per slab and panel
-constexpr int kRG = kRK / 16;
+constexpr int kRing = 2;   // units of 16 k in flight
 
 template <typename T>
 __global__ void __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(2, 2)))
@@ -297,7 +300,7 @@ rotate_kernel(const T* X, int64_t ldx, const T* __restrict__ Z, int64_t ldz, T* 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
   const int lane = threadIdx.x % 64, q = lane / 16, cl = lane % 16;
   for (int c0 = (N2 - 1) / kRK * kRK; c0 >= 0; c0 -= kRK) {
-    const int G = min(kRG, (N2 - c0 + 15) / 16);
+    const int G = min(kRK / 16, (N2 - c0 + 15) / 16);
     const int g[4] = {G - 1 - wave, G - 8 + wave, G - 9 - wave, G - 16 + wave};   // negative: none
     Acc acc[2][4];
 #pragma unroll
@@ -331,38 +334,52 @@ rotate_kernel(const T* X, int64_t ldx, const T* __restrict__ Z, int64_t ldz, T* 
           rsrc(Z + static_cast<int64_t>(kb) * ldz, static_cast<uint32_t>((static_cast<int64_t>(rows - 1) * ldz + N2) * sizeof(T)));
       const uint32_t zstep = static_cast<uint32_t>(ldz * 4 * sizeof(T));   // 4 rows of Z
       const uint32_t zlane = static_cast<uint32_t>((q * ldz + c0 + cl) * sizeof(T));
-      auto load = [&](T (&b)[4][4], int kc) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const bool on = g[i] >= 0 && !(diag && kc > g[i]) && kc * 16 < nk;
-          const uint32_t o = zlane + kc * 4 * zstep + static_cast<uint32_t>(g[i] * 16 * static_cast<int>(sizeof(T)));
-#pragma unroll
-          for (int s = 0; s < 4; ++s) b[s][i] = bload_group<T, 0>(rz, on ? o + s * zstep : kBeyond);
-        }
-      };
-      auto compute = [&](const T (&b)[4][4], int kc) {
-        T a[4][2];
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-#pragma unroll
-          for (int r = 0; r < 2; ++r) a[s][r] = xs[r * 16 + cl][kc * 16 + s * 4 + q];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          if (g[i] < 0 || (diag && kc > g[i])) continue;
-#pragma unroll
-          for (int s = 0; s < 4; ++s)
-#pragma unroll
-            for (int r = 0; r < 2; ++r) acc[r][i] = Mfma<T>::mma(a[s][r], b[s][i], acc[r][i]);
-        }
-      };
+      // units of 16 k of one group, group after group; the list of loads runs
+      // kRing units ahead of the multiplications
       const int nkc = (nk + 15) / 16;
-      T b0[4][4], b1[4][4];
-      load(b0, 0);
-      for (int kc = 0; kc < nkc; kc += 2) {
-        load(b1, kc + 1);
-        compute(b0, kc);
-        load(b0, kc + 2);
-        if (kc + 1 < nkc) compute(b1, kc + 1);
+      int len[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) len[i] = g[i] < 0 ? 0 : (diag ? min(g[i] + 1, nkc) : nkc);
+      int lg = 0, lk = 0;                     // group and unit of the next load
+      T b[kRing][4];
+      auto load = [&](T (&u)[4]) {
+        const int n = lg == 0 ? len[0] : lg == 1 ? len[1] : lg == 2 ? len[2] : lg == 3 ? len[3] : 0;
+        const int gi = lg == 0 ? g[0] : lg == 1 ? g[1] : lg == 2 ? g[2] : g[3];
+        const uint32_t o = zlane + lk * 4 * zstep + static_cast<uint32_t>(gi * 16 * static_cast<int>(sizeof(T)));
+#pragma unroll
+        for (int s = 0; s < 4; ++s) u[s] = bload_group<T, 0>(rz, lk < n ? o + s * zstep : kBeyond);
+        ++lk;
+        if (lk % kRing == 0 && lk >= n) {
+          lk = 0;
+          ++lg;
+          if (lg == 1 && len[1] == 0) ++lg;
+          if (lg == 2 && len[2] == 0) ++lg;
+          if (lg == 3 && len[3] == 0) ++lg;
+        }
+      };
+      if (len[0] == 0) continue;
+#pragma unroll
+      for (int u = 0; u < kRing; ++u) load(b[u]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+#pragma unroll 1
+        for (int kc = 0; kc < len[i]; kc += kRing) {
+#pragma unroll
+          for (int u = 0; u < kRing; ++u) {
+            if (kc + u < len[i]) {
+              T a[4][2];
+#pragma unroll
+              for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int r = 0; r < 2; ++r) a[s][r] = xs[r * 16 + cl][(kc + u) * 16 + s * 4 + q];
+#pragma unroll
+              for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int r = 0; r < 2; ++r) acc[r][i] = Mfma<T>::mma(a[s][r], b[u][s], acc[r][i]);
+            }
+            load(b[u]);
+          }
+        }
       }
     }
 #pragma unroll
