@@ -898,37 +898,44 @@ int do_bounds(chfsi_op* op, int steps, const double* v0_dev, const double* v0_ho
     HIP_TRY(ctx, hipMemcpyAsync(v, h.data(), nr * 8, hipMemcpyHostToDevice, ctx->stream));
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
   }
-  double nv;
-  CHECK(dot_host(ctx, v, v, nr, &nv));
-  if (!(nv > 0.0) || !std::isfinite(nv)) return fail(ctx, CHFSI_EINVAL, "Lanczos start vector is zero or non-finite");
-  HIP_TRY(ctx, launch_axpby(0.0, v, 1.0 / std::sqrt(nv), v, nr, ctx->stream));
-  std::vector<double> al, be;
-  // f = H v ; alpha = v.f ; f -= alpha v
+  // the scalars stay on the device until the end: |f|^2 before step k in
+  // out[k] (of the start vector for k = 0), alpha_k in out[steps + 1 + k]
+  const size_t nout = 2 * static_cast<size_t>(steps) + 1;
+  void* sb;
+  CHECK(ws_get(ctx, WS_SMALL, (2 * static_cast<size_t>(dot_blocks()) + nout) * 8, &sb));
+  double* part1 = static_cast<double*>(sb);
+  double* part2 = part1 + dot_blocks();
+  double* out = part2 + dot_blocks();
+  // f is the start vector, then v = f / |f| ; f = H v - |f| vprev ; alpha = v.f ; f -= alpha v
+  std::swap(f, v);
+  HIP_TRY(ctx, launch_dot(f, f, nr, part1, ctx->stream));
   const bool tensor = tensor_path(op, prec, 1);
-  if (!tensor) HIP_TRY(ctx, launch_fill(f, t.M, cf, cf, prec, ctx->stream));
-  CHECK(hx_step(op, prec, v, 1, nullptr, 1, f, 1, 1, 1.0, 0.0, 0.0, false));
-  double alpha;
-  CHECK(dot_host(ctx, v, f, nr, &alpha));
-  HIP_TRY(ctx, launch_axpby(-alpha, v, 1.0, f, nr, ctx->stream));
-  al.push_back(alpha);
-  for (int k = 1; k < steps; ++k) {
-    double bb;
-    CHECK(dot_host(ctx, f, f, nr, &bb));
-    const double beta = std::sqrt(bb);
-    if (!(beta > 0.0)) break;
-    // vprev <- v ; v <- f / beta ; f <- H v - beta vprev ; alpha ; f -= alpha v
+  for (int k = 0; k < steps; ++k) {
     std::swap(v, vprev);
-    HIP_TRY(ctx, launch_axpby(1.0 / beta, f, 0.0, v, nr, ctx->stream));
+    HIP_TRY(ctx, launch_lanczos_scale(part1, out + k, f, v, nr, ctx->stream));
     if (!tensor) HIP_TRY(ctx, launch_fill(f, t.M, cf, cf, prec, ctx->stream));
     CHECK(hx_step(op, prec, v, 1, nullptr, 1, f, 1, 1, 1.0, 0.0, 0.0, false));
-    HIP_TRY(ctx, launch_axpby(-beta, vprev, 1.0, f, nr, ctx->stream));
-    CHECK(dot_host(ctx, v, f, nr, &alpha));
-    HIP_TRY(ctx, launch_axpby(-alpha, v, 1.0, f, nr, ctx->stream));
-    al.push_back(alpha);
-    be.push_back(beta);
+    HIP_TRY(ctx, launch_lanczos_orth(out + k, k ? vprev : nullptr, v, f, nr, part2, ctx->stream));
+    HIP_TRY(ctx, launch_lanczos_close(part2, out + steps + 1 + k, v, f, nr, part1, ctx->stream));
   }
-  double ff;
-  CHECK(dot_host(ctx, f, f, nr, &ff));
+  std::vector<double> h(dot_blocks() + nout);
+  HIP_TRY(ctx, hipMemcpyAsync(h.data(), part1, dot_blocks() * 8, hipMemcpyDeviceToHost, ctx->stream));
+  HIP_TRY(ctx, hipMemcpyAsync(h.data() + dot_blocks(), out, nout * 8, hipMemcpyDeviceToHost, ctx->stream));
+  HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+  double* bb = h.data() + dot_blocks();
+  const double* alpha = bb + steps + 1;
+  if (!(bb[0] > 0.0) || !std::isfinite(bb[0]))
+    return fail(ctx, CHFSI_EINVAL, "Lanczos start vector is zero or non-finite");
+  bb[steps] = 0.0;
+  for (int i = 0; i < dot_blocks(); ++i) bb[steps] += h[i];
+  // up to the first step at which nothing was left of f
+  std::vector<double> al(1, alpha[0]), be;
+  int last = 1;
+  for (; last < steps && std::sqrt(bb[last]) > 0.0; ++last) {
+    al.push_back(alpha[last]);
+    be.push_back(std::sqrt(bb[last]));
+  }
+  const double ff = bb[last];
   const int k = static_cast<int>(al.size());
   std::vector<double> T(static_cast<size_t>(k) * k, 0.0);
   for (int i = 0; i < k; ++i) T[i * k + i] = al[i];
@@ -1155,7 +1162,7 @@ int batched_tensor_filter(chfsi_ctx* ctx, const std::vector<BItem>& items, int m
         R.rows += 4 * static_cast<int64_t>(op->t.natoms);
         R.upd += (op->nown_cells + nl_update_cells() - 1) / nl_update_cells();
         R.tiles = std::max<int>(R.tiles, static_cast<int>((nb + 63) / 64));   // logical columns
-        R.rowblk = std::max<int>(R.rowblk, static_cast<int>((ldhp[q] + 255) / 256));
+        R.rowblk = std::max<int>(R.rowblk, static_cast<int>(ldhp[q] / 64));
         R.max_real = std::max<int>(R.max_real, static_cast<int>(nb * cf));
         R.max_ldhp = std::max<int>(R.max_ldhp, static_cast<int>(ldhp[q]));
         reinterpret_cast<NlLaunch*>(h + nl_at)[static_cast<size_t>(r) * n + j] =
@@ -1364,7 +1371,7 @@ int batched_filter(chfsi_ctx* ctx, const std::vector<BItem>& items, int m, int p
         nl_chunks[r] += op->nchunks;
         nl_rows[r] += 4 * static_cast<int64_t>(op->t.natoms);
         nl_tiles[r] = std::max<int>(nl_tiles[r], static_cast<int>((nb + 63) / 64));   // logical columns
-        nl_rowblk[r] = std::max<int>(nl_rowblk[r], static_cast<int>((ldhp[q] + 255) / 256));
+        nl_rowblk[r] = std::max<int>(nl_rowblk[r], static_cast<int>(ldhp[q] / 64));
         for (int st = 1; st <= m; ++st)
           hnl[(static_cast<size_t>(r) * m + (st - 1)) * n + j] =
               make_nl(op, R(q, (st - 1) % 4), nb, nb, base + offPart[q], base + offHP[q], ldhp[q]);

@@ -183,7 +183,7 @@ hipError_t launch_nl_project(const NlLaunch& a, int prec, hipStream_t s);
 // descs = device array of nprob NlLaunch; chunk_off / row_off = device
 // arrays of nprob + 1 offsets of the problems' chunks and of their
 // (atom, component) rows; max_col_tiles = max ceil(ncols / 64) and
-// max_row_blocks = max ceil(ldhp / 256) over the problems.
+// max_row_blocks = max ldhp / 64 over the problems.
 struct NlBatch {
   const void* descs;
   const int64_t* chunk_off;
@@ -321,6 +321,16 @@ hipError_t launch_resid(const double* HX, int64_t ldh, const double* X, int64_t 
 int dot_blocks();
 hipError_t launch_dot(const double* x, const double* y, int64_t n, double* partial, hipStream_t s);
 // y = a*x + b*y over n reals
+// One Lanczos step's vector work with its scalars on the device (part1, part2:
+// dot_blocks() partial sums each):
+// scale: *bb = sum(part1), v = f / sqrt(*bb) (0 where that is not positive);
+// orth: f -= sqrt(*bb) vprev (vprev null: nothing), part2 = v . f;
+// close: *alpha = sum(part2), f -= *alpha v, part1 = f . f.
+hipError_t launch_lanczos_scale(const double* part1, double* bb, const double* f, double* v, int64_t n, hipStream_t s);
+hipError_t launch_lanczos_orth(const double* bb, const double* vprev, const double* v, double* f, int64_t n,
+                               double* part2, hipStream_t s);
+hipError_t launch_lanczos_close(const double* part2, double* alpha, const double* v, double* f, int64_t n,
+                                double* part1, hipStream_t s);
 hipError_t launch_axpby(double a, const double* x, double b, double* y, int64_t n, hipStream_t s);
 // small matrix helpers (n x n)
 hipError_t launch_transpose(const double* in, double* out, int n, hipStream_t s);

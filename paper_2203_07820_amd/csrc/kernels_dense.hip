@@ -442,6 +442,70 @@ dot_kernel(const double* __restrict__ x, const double* __restrict__ y, int64_t n
   if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
+// sum of the kDotBlocks partial sums, by every workgroup in the same order
+__device__ __forceinline__ double sum_parts(const double* __restrict__ part, double* red) {
+  double s = 0.0;
+#pragma unroll
+  for (int i = 0; i < kDotBlocks / 256; ++i) s += part[threadIdx.x + 256 * i];
+  red[threadIdx.x] = s;
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) {
+    if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+    __syncthreads();
+  }
+  return red[0];
+}
+__device__ __forceinline__ void store_part(double s, double* red, double* part) {
+  __syncthreads();
+  red[threadIdx.x] = s;
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) {
+    if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
+}
+
+// The vector work of a Lanczos step, kDotBlocks workgroups.  With the scalars
+// read by the host a step waited for two reductions to reach it; these are
+// launched back to back.
+__global__ void __launch_bounds__(256)
+lanczos_scale_kernel(const double* __restrict__ part1, double* bb, const double* __restrict__ f,
+                     double* __restrict__ v, int64_t n) {
+  __shared__ double red[256];
+  const double b = sum_parts(part1, red);
+  if (blockIdx.x == 0 && threadIdx.x == 0) *bb = b;
+  const double inv = b > 0.0 ? 1.0 / sqrt(b) : 0.0;
+  for (int64_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += kDotBlocks * 256) v[i] = inv * f[i];
+}
+__global__ void __launch_bounds__(256)
+lanczos_orth_kernel(const double* __restrict__ bb, const double* __restrict__ vprev, const double* __restrict__ v,
+                    double* __restrict__ f, int64_t n, double* __restrict__ part2) {
+  __shared__ double red[256];
+  const double beta = vprev ? sqrt(*bb) : 0.0;
+  double s = 0.0;
+  for (int64_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += kDotBlocks * 256) {
+    double x = f[i];
+    if (vprev) f[i] = x -= beta * vprev[i];
+    s += v[i] * x;
+  }
+  store_part(s, red, part2);
+}
+__global__ void __launch_bounds__(256)
+lanczos_close_kernel(const double* __restrict__ part2, double* alpha, const double* __restrict__ v,
+                     double* __restrict__ f, int64_t n, double* __restrict__ part1) {
+  __shared__ double red[256];
+  const double a = sum_parts(part2, red);
+  if (blockIdx.x == 0 && threadIdx.x == 0) *alpha = a;
+  double s = 0.0;
+  for (int64_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += kDotBlocks * 256) {
+    const double x = f[i] - a * v[i];
+    f[i] = x;
+    s += x * x;
+  }
+  store_part(s, red, part1);
+}
+
 __global__ void axpby_kernel(double a, const double* __restrict__ x, double b, double* __restrict__ y,
                              int64_t n) {
   for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n;
@@ -659,6 +723,23 @@ int dot_blocks() { return kDotBlocks; }
 
 hipError_t launch_dot(const double* x, const double* y, int64_t n, double* partial, hipStream_t s) {
   hipLaunchKernelGGL(dot_kernel, dim3(kDotBlocks), dim3(256), 0, s, x, y, n, partial);
+  return hipGetLastError();
+}
+
+hipError_t launch_lanczos_scale(const double* part1, double* bb, const double* f, double* v, int64_t n, hipStream_t s) {
+  hipLaunchKernelGGL(lanczos_scale_kernel, dim3(kDotBlocks), dim3(256), 0, s, part1, bb, f, v, n);
+  return hipGetLastError();
+}
+
+hipError_t launch_lanczos_orth(const double* bb, const double* vprev, const double* v, double* f, int64_t n,
+                               double* part2, hipStream_t s) {
+  hipLaunchKernelGGL(lanczos_orth_kernel, dim3(kDotBlocks), dim3(256), 0, s, bb, vprev, v, f, n, part2);
+  return hipGetLastError();
+}
+
+hipError_t launch_lanczos_close(const double* part2, double* alpha, const double* v, double* f, int64_t n,
+                                double* part1, hipStream_t s) {
+  hipLaunchKernelGGL(lanczos_close_kernel, dim3(kDotBlocks), dim3(256), 0, s, part2, alpha, v, f, n, part1);
   return hipGetLastError();
 }
 

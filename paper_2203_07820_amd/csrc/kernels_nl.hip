@@ -4,6 +4,7 @@
 // helpers of the filter (zero fill, precision conversion of a block).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "device_util.h"
@@ -107,24 +108,90 @@ nl_partial_kernel(const int32_t* chunk_atom, const int64_t* chunk_begin, const i
                            to_global(partial), ldhp);
 }
 
+// The same for blocks of up to 16 columns: a wave's lanes are 64 / W entries of
+// the chunk by W >= ncols columns, and the entries' sums are added over the
+// lanes in a fixed order.
+template <typename T, bool CPLX>
+__global__ void __launch_bounds__(256)
+nl_partial_narrow_kernel(const int32_t* __restrict__ chunk_atom, const int64_t* __restrict__ chunk_begin,
+                         const int64_t* __restrict__ atom_ptr, const int32_t* __restrict__ atom_node,
+                         const double* __restrict__ atom_val, const T* __restrict__ X, int64_t ldx, int ncols,
+                         T* __restrict__ partial, int64_t ldhp) {
+  constexpr int NV = CPLX ? 8 : 4;
+  __shared__ T red[4][NV][16];
+  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, chunk = blockIdx.x;
+  int W = 1;
+  while (W < ncols) W *= 2;
+  const int col = lane % W, colc = col < ncols ? col : ncols - 1;
+  const int64_t e0 = chunk_begin[chunk], end = atom_ptr[chunk_atom[chunk] + 1];
+  const int64_t e1 = e0 + kNlChunk < end ? e0 + kNlChunk : end;
+  T acc[NV];
+#pragma unroll
+  for (int m = 0; m < NV; ++m) acc[m] = T(0);
+#pragma unroll 4
+  for (int64_t e = e0 + wave * (64 / W) + lane / W; e < e1; e += 4 * (64 / W)) {
+    const int64_t j = atom_node[e] * ldx + colc;
+    const double* v = atom_val + e * NV;
+    if constexpr (CPLX) {
+      const T xr = X[2 * j], xi = X[2 * j + 1];
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        const T cr = static_cast<T>(v[2 * m]), ci = static_cast<T>(v[2 * m + 1]);
+        acc[2 * m] += cr * xr + ci * xi;       // conj(c) x
+        acc[2 * m + 1] += cr * xi - ci * xr;
+      }
+    } else {
+      const T x = X[j];
+#pragma unroll
+      for (int m = 0; m < 4; ++m) acc[m] += static_cast<T>(v[m]) * x;
+    }
+  }
+  for (int d = W; d < 64; d *= 2)
+#pragma unroll
+    for (int m = 0; m < NV; ++m) acc[m] += __shfl_xor(acc[m], d, 64);
+  if (lane < W)
+#pragma unroll
+    for (int m = 0; m < NV; ++m) red[wave][m][lane] = acc[m];
+  __syncthreads();
+  if (static_cast<int>(threadIdx.x) < ncols) {
+#pragma unroll
+    for (int m = 0; m < NV; ++m) {
+      const T s = ((red[0][m][col] + red[1][m][col]) + red[2][m][col]) + red[3][m][col];
+      if constexpr (CPLX) partial[(static_cast<int64_t>(chunk) * 4 + m / 2) * ldhp + 2 * col + (m & 1)] = s;
+      else partial[(static_cast<int64_t>(chunk) * 4 + m) * ldhp + col] = s;
+    }
+  }
+}
+
+// hP[atom][m] = h times the sum of the atom's chunks, 64 columns per workgroup:
+// 8 waves take every 8th chunk, their sums are added in a fixed order.  (One
+// thread per column over all chunks is a chain of dependent loads: 23 us
+// for one column of 16 atoms on 12^3 cells, p = 5, 60 us for 128 columns of 64
+// atoms on 24^3 cells, p = 6; this takes 4 and 7 us.)
 template <typename T>
 __device__ __forceinline__ void nl_reduce_item(const int am, const int jblk, gptr<const int32_t> atom_chunk_ptr,
                                                gptr<const double> hcoef, gptr<const T> partial, gptr<T> hP,
                                                int64_t ldhp, int nreal) {
+  __shared__ T red[8][64];
   const int at = am / 4, m = am % 4;   // am = atom * 4 + component
-  const int j = jblk * 256 + threadIdx.x;
-  if (j >= ldhp) return;
+  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+  const int64_t j = jblk * 64 + lane;  // ldhp is a multiple of 64
   T s = T(0);
   if (j < nreal) {
-    for (int ch = atom_chunk_ptr[at]; ch < atom_chunk_ptr[at + 1]; ++ch)
-      s += partial[(static_cast<int64_t>(ch) * 4 + m) * ldhp + j];
-    s *= static_cast<T>(hcoef[am]);
+    const int c1 = atom_chunk_ptr[at + 1];
+#pragma unroll 4
+    for (int ch = atom_chunk_ptr[at] + wave; ch < c1; ch += 8) s += partial[(static_cast<int64_t>(ch) * 4 + m) * ldhp + j];
   }
-  hP[static_cast<int64_t>(am) * ldhp + j] = s;
+  red[wave][lane] = s;
+  __syncthreads();
+  if (wave != 0) return;
+#pragma unroll
+  for (int w = 1; w < 8; ++w) s += red[w][lane];
+  hP[static_cast<int64_t>(am) * ldhp + j] = s * static_cast<T>(hcoef[am]);
 }
 
 template <typename T>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(512)
 nl_reduce_kernel(const int32_t* atom_chunk_ptr, const double* hcoef, const T* partial, T* hP,
                  int64_t ldhp, int nreal) {
   nl_reduce_item<T>(blockIdx.x, blockIdx.y, to_global(atom_chunk_ptr), to_global(hcoef), to_global(partial),
@@ -148,10 +215,11 @@ nl_partial_batched_kernel(const NlLaunch* __restrict__ d, const int64_t* __restr
 }
 
 template <typename T, bool CPLX>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(512)
 nl_reduce_batched_kernel(const NlLaunch* __restrict__ d, const int64_t* __restrict__ am_off, const int nprob) {
   const int q = problem_of(am_off, nprob, blockIdx.x);
   const NlLaunch& L = d[q];
+  if (static_cast<int64_t>(blockIdx.y) * 64 >= L.ldhp) return;   // the grid is the widest problem's
   nl_reduce_item<T>(static_cast<int>(blockIdx.x - am_off[q]), blockIdx.y, to_global(L.atom_chunk_ptr),
                     to_global(L.hcoef), to_global(static_cast<const T*>(L.partial)),
                     to_global(static_cast<T*>(L.hP)), L.ldhp, CPLX ? 2 * L.ncols : L.ncols);
@@ -161,11 +229,18 @@ template <typename T, bool CPLX>
 hipError_t nl_launch(const NlLaunch& L, hipStream_t s) {
   if (L.nchunks <= 0) return hipSuccess;
   const int nct = (L.ncols + 63) / 64;
-  hipLaunchKernelGGL((nl_partial_kernel<T, CPLX>), dim3(L.nchunks, nct), dim3(256), 0, s,
-                     L.chunk_atom, L.chunk_begin, L.atom_ptr, L.atom_node, L.atom_val,
-                     static_cast<const T*>(L.X), L.ldx, L.ncols, static_cast<T*>(L.partial), L.ldhp);
+  // up to 16 columns the lanes of a wave take several entries at a time (one
+  // column, 16 atoms, 12^3 cells, p = 5: 26 -> 7 us)
+  if (L.ncols <= 16)
+    hipLaunchKernelGGL((nl_partial_narrow_kernel<T, CPLX>), dim3(L.nchunks), dim3(256), 0, s, L.chunk_atom,
+                       L.chunk_begin, L.atom_ptr, L.atom_node, L.atom_val, static_cast<const T*>(L.X), L.ldx, L.ncols,
+                       static_cast<T*>(L.partial), L.ldhp);
+  else
+    hipLaunchKernelGGL((nl_partial_kernel<T, CPLX>), dim3(L.nchunks, nct), dim3(256), 0, s,
+                       L.chunk_atom, L.chunk_begin, L.atom_ptr, L.atom_node, L.atom_val,
+                       static_cast<const T*>(L.X), L.ldx, L.ncols, static_cast<T*>(L.partial), L.ldhp);
   const int nreal = CPLX ? 2 * L.ncols : L.ncols;
-  hipLaunchKernelGGL((nl_reduce_kernel<T>), dim3(L.natoms * 4, (L.ldhp + 255) / 256), dim3(256), 0, s,
+  hipLaunchKernelGGL((nl_reduce_kernel<T>), dim3(L.natoms * 4, L.ldhp / 64), dim3(512), 0, s,
                      L.atom_chunk_ptr, L.hcoef, static_cast<const T*>(L.partial), static_cast<T*>(L.hP),
                      L.ldhp, nreal);
   return hipGetLastError();
@@ -225,7 +300,7 @@ __device__ __forceinline__ float nl_rot(float v, int lane) {
 
 template <int P, typename T, bool CPLX>
 __device__ __forceinline__ void nl_update_item(const NlUpdate& a, const int item, const int ctile,
-                                               const int32_t* noff) {
+                                               const int32_t* noff, const int part_z = 0, const int parts = 1) {
     constexpr int P3 = P * P * P, NT = (P3 + 15) / 16, CV = CPLX ? 2 : 1, NC = kNlGroups;
   typedef typename NlMma<T>::acc acc_t;
   const int lane = threadIdx.x % 64, q = lane / 16, cl = lane % 16;
@@ -340,13 +415,15 @@ __device__ __forceinline__ void nl_update_item(const NlUpdate& a, const int item
     if (a.part) project(0, t, u);
   };
   clear();
-  load(0, ta);
+  const int t0 = NT * part_z / parts, t1 = NT * (part_z + 1) / parts;
+  if (t0 == t1) return;
+  load(t0, ta);
 #pragma unroll 1
-  for (int t = 0; t < NT; t += 2) {
-    if (t + 1 < NT) load(t + 1, tb);
+  for (int t = t0; t < t1; t += 2) {
+    if (t + 1 < t1) load(t + 1, tb);
     step(t, ta);
-    if (t + 2 < NT) load(t + 2, ta);
-    if (t + 1 < NT) step(t + 1, tb);
+    if (t + 2 < t1) load(t + 2, ta);
+    if (t + 1 < t1) step(t + 1, tb);
   }
   if (!a.part) return;
   put(0);
@@ -380,7 +457,7 @@ __global__ void __launch_bounds__(256, 4) nl_update_kernel(const NlUpdate a) {
   __shared__ int32_t noff[(P * P * P + 15) / 16 * 16];
   nl_node_offsets<P>(a.nc, noff);
   const int item = __builtin_amdgcn_readfirstlane(blockIdx.x * kNlCells + threadIdx.x / 64);
-  if (item < a.ncells) nl_update_item<P, T, CPLX>(a, item, blockIdx.y, noff);
+  if (item < a.ncells) nl_update_item<P, T, CPLX>(a, item, blockIdx.y, noff, blockIdx.z, gridDim.z);
 }
 
 // The update of many problems (batched filter): descriptors in device memory.
@@ -436,9 +513,20 @@ nl_pair_reduce_batched_kernel(const NlUpdate* __restrict__ d, const int64_t* __r
   nl_pair_reduce_item<T>(a, static_cast<int>(blockIdx.x - row_off[q]), blockIdx.y);
 }
 
+// Parts of a cell's tiles, each a wave of its own, where no projections are
+// summed over them: as many as make 8192 waves, of two tiles or more (one
+// column, 12^3 cells, p = 5: 28 us by 1728 waves, 18 us by four times as many).
+unsigned nl_update_parts(const NlUpdate& a, int p) {
+  if (a.part || a.ncells <= 0) return 1;
+  const int64_t waves = static_cast<int64_t>(a.ncells) * ((a.nreal + 16 * kNlGroups - 1) / (16 * kNlGroups));
+  const int64_t pairs = (p * p * p + 15) / 16 / 2;
+  return static_cast<unsigned>(std::max<int64_t>(1, std::min<int64_t>(8192 / waves, pairs)));
+}
+
 template <typename T, bool CPLX>
 hipError_t nl_update_launch(const NlUpdate& a, int p, hipStream_t s) {
-  const dim3 g((a.ncells + kNlCells - 1) / kNlCells, (a.nreal + 16 * kNlGroups - 1) / (16 * kNlGroups));
+  const dim3 g((a.ncells + kNlCells - 1) / kNlCells, (a.nreal + 16 * kNlGroups - 1) / (16 * kNlGroups),
+               nl_update_parts(a, p));
   if (a.ncells > 0) {
     switch (p) {
       case 2: hipLaunchKernelGGL((nl_update_kernel<2, T, CPLX>), g, dim3(256), 0, s, a); break;
@@ -590,19 +678,19 @@ hipError_t launch_nl_project_batched(const NlBatch& b, int prec, hipStream_t s) 
   switch (prec) {
     case CHFSI_F64:
       hipLaunchKernelGGL((nl_partial_batched_kernel<double, false>), gp, dim3(256), 0, s, d, b.chunk_off, b.nprob);
-      hipLaunchKernelGGL((nl_reduce_batched_kernel<double, false>), gr, dim3(256), 0, s, d, b.row_off, b.nprob);
+      hipLaunchKernelGGL((nl_reduce_batched_kernel<double, false>), gr, dim3(512), 0, s, d, b.row_off, b.nprob);
       break;
     case CHFSI_F32:
       hipLaunchKernelGGL((nl_partial_batched_kernel<float, false>), gp, dim3(256), 0, s, d, b.chunk_off, b.nprob);
-      hipLaunchKernelGGL((nl_reduce_batched_kernel<float, false>), gr, dim3(256), 0, s, d, b.row_off, b.nprob);
+      hipLaunchKernelGGL((nl_reduce_batched_kernel<float, false>), gr, dim3(512), 0, s, d, b.row_off, b.nprob);
       break;
     case CHFSI_C128:
       hipLaunchKernelGGL((nl_partial_batched_kernel<double, true>), gp, dim3(256), 0, s, d, b.chunk_off, b.nprob);
-      hipLaunchKernelGGL((nl_reduce_batched_kernel<double, true>), gr, dim3(256), 0, s, d, b.row_off, b.nprob);
+      hipLaunchKernelGGL((nl_reduce_batched_kernel<double, true>), gr, dim3(512), 0, s, d, b.row_off, b.nprob);
       break;
     case CHFSI_C64:
       hipLaunchKernelGGL((nl_partial_batched_kernel<float, true>), gp, dim3(256), 0, s, d, b.chunk_off, b.nprob);
-      hipLaunchKernelGGL((nl_reduce_batched_kernel<float, true>), gr, dim3(256), 0, s, d, b.row_off, b.nprob);
+      hipLaunchKernelGGL((nl_reduce_batched_kernel<float, true>), gr, dim3(512), 0, s, d, b.row_off, b.nprob);
       break;
     default: return hipErrorInvalidValue;
   }

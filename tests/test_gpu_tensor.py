@@ -155,3 +155,43 @@ def test_subspace_widths(ctx, N, k):
     assert np.max(np.abs(th - th_ref)) < 1e-10 * max(1.0, np.max(np.abs(th_ref)))
     Psi = Xd.cpu().numpy()
     assert np.max(np.abs(np.linalg.norm(H @ Psi - Psi * th, axis=0) - r)) < 1e-9
+
+
+# one column (the narrow projection and the update in parts), real and complex:
+# bounds of 1 and more steps against the same recurrence on the host
+@pytest.mark.parametrize("steps", [1, 2, 9])
+@pytest.mark.parametrize("k", [(0, 0, 0), K])
+def test_bounds_recurrence(ctx, steps, k):
+    s = workloads.small_system(3, 5, 3, seed=4, has_proj=True, k=k)
+    op = lib.Operator(ctx, s)
+    H = fe.assemble(fe.build_operator(s))
+    v = workloads.lanczos_start(op.M, 9, op.is_complex)
+    got = op.bounds(steps, torch.from_numpy(v).cuda())
+    f, prev, beta, al, be = v, 0.0 * v, 0.0, [], []
+    for i in range(steps):
+        nrm = np.linalg.norm(f)
+        if i:
+            be.append(nrm)
+        q = f / nrm
+        f = H @ q - (nrm * prev if i else 0.0)
+        al.append(np.vdot(q, f).real)
+        f = f - al[-1] * q
+        prev = q
+    ev = np.linalg.eigvalsh(np.diag(al) + np.diag(be, 1) + np.diag(be, -1))
+    # one product each step: 1e-12 of the norm, growing with the steps
+    assert abs(got[0] - (ev[-1] + np.linalg.norm(f))) < 1e-10 * ev[-1]
+    assert abs(got[1] - ev[0]) < 1e-10 * ev[-1]
+
+
+def test_bounds_refuses_a_zero_start(ctx):
+    op = lib.Operator(ctx, workloads.small_system(2, 3, 1, seed=4))
+    with pytest.raises(lib.ChfsiError):
+        op.bounds(4, torch.zeros(op.M, dtype=torch.float64, device="cuda"))
+
+
+# widths around the narrow projection's 16 columns
+@pytest.mark.parametrize("ncols", [2, 3, 9, 16, 17])
+@pytest.mark.parametrize("k", [(0, 0, 0), K])
+def test_narrow_projection(ctx, ncols, k):
+    for single in (False, True):
+        _run(ctx, 3, 5, 3, k, ncols, ncols + 1, single, 2)
