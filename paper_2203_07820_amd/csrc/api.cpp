@@ -1128,6 +1128,10 @@ int batched_tensor_filter(chfsi_ctx* ctx, const std::vector<BItem>& items, int m
       work += static_cast<double>(items[q].op->t.M) * R.width.back();
     }
     const int na = static_cast<int>(R.act.size());
+    // the longest workgroups (whole columns of cells) first, so that the short
+    // ones fill the launch's end
+    std::stable_sort(R.act.begin(), R.act.end(), [&](int a, int b) { return ncs[a] > ncs[b]; });
+    for (int k = 0; k < na; ++k) R.width[k] = std::min<int64_t>(Bq[R.act[k]], items[R.act[k]].ncols - r * Bq[R.act[k]]);
     for (int k = 0; k < na; ++k) {
       const int q = R.act[k];
       chfsi_op* op = items[q].op;

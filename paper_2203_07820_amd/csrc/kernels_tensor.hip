@@ -540,14 +540,16 @@ __global__ void __attribute__((amdgpu_flat_work_group_size(64 * TsShape<P, T, CP
 tensor_hx_kernel(const TsArgs<T> kernel_args, const TsArgs<T>* descs, const int64_t* item_off, const int nprob) {
   using Sh = TsShape<P, T, CPLX, TX>;
   __shared__ typename Lane<T>::V lds[2 * Sh::LBUF];
-  int w = xcd_order(blockIdx.x, gridDim.x);
+  int pid = blockIdx.x, nblk = gridDim.x;
   cptr<TsArgs<T>> args = (cptr<TsArgs<T>>)__builtin_amdgcn_kernarg_segment_ptr();
   if (nprob > 0) {   // the arguments come first in the segment; a batch has them in a device table
-    const int q = __builtin_amdgcn_readfirstlane(problem_of(item_off, nprob, w));
-    w -= static_cast<int>(item_off[q]);
+    const int q = __builtin_amdgcn_readfirstlane(problem_of(item_off, nprob, pid));
+    const int first = static_cast<int>(item_off[q]);
+    nblk = static_cast<int>(item_off[q + 1]) - first;
+    pid -= first;    // every problem over all XCDs: their workgroups differ in length
     args = to_const(descs + q);
   }
-  ts_workgroup<P, T, CPLX, TX>(args, w, lds);
+  ts_workgroup<P, T, CPLX, TX>(args, xcd_order(pid, nblk), lds);
 }
 
 // Cells per chunk in z.  A chunk repeats the planes of the cell below it, so
