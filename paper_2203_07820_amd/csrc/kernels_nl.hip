@@ -267,7 +267,10 @@ hipError_t nl_launch(const NlLaunch& L, hipStream_t s) {
 // projectors of 4 atoms fill its other 16 rows.  Cells with more than 4 atoms
 // read their rows again for the further atoms' projections.  32 columns: with
 // 16 the projector values are read twice as often (3 % of a filter), with 64
-// two waves per SIMD fit instead of four (3 % on the 12^3 box).
+// two waves per SIMD fit instead of four (3 % on the 12^3 box).  Requesting a
+// tile's projector values together takes 3 % off the filter on the 12^3 box;
+// complex FP64 and the batched kernel would spill registers for it and are 6-8 %
+// slower that way.
 constexpr int kNlGroups = 2;   // groups of 16 real columns per wave
 typedef double nd4 __attribute__((ext_vector_type(4)));
 typedef float nf4 __attribute__((ext_vector_type(4)));
@@ -298,7 +301,7 @@ __device__ __forceinline__ float nl_rot(float v, int lane) {
   return (lane & 1) ? -o : o;
 }
 
-template <int P, typename T, bool CPLX>
+template <int P, typename T, bool CPLX, bool TOGETHER>
 __device__ __forceinline__ void nl_update_item(const NlUpdate& a, const int item, const int ctile,
                                                const int32_t* noff, const int part_z = 0, const int parts = 1) {
     constexpr int P3 = P * P * P, NT = (P3 + 15) / 16, CV = CPLX ? 2 : 1, NC = kNlGroups;
@@ -343,10 +346,11 @@ __device__ __forceinline__ void nl_update_item(const NlUpdate& a, const int item
 #pragma unroll
   for (int g = 0; g < 4; ++g)
     if (g < np) load_h(g, hb[g]);
-  auto add = [&](int g, int t, const T (&h)[NC], Tile& u) {
-    T cv[CV];
+  auto load_c = [&](int g, int t, T (&cv)[CV]) {
 #pragma unroll
     for (int v = 0; v < CV; ++v) cv[v] = val[((static_cast<int64_t>(g) * NT + t) * CV + v) * 64 + lane];
+  };
+  auto add = [&](const T (&cv)[CV], const T (&h)[NC], Tile& u) {
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       acc_t d = {u.y[c][0], u.y[c][1], u.y[c][2], u.y[c][3]};
@@ -362,23 +366,25 @@ __device__ __forceinline__ void nl_update_item(const NlUpdate& a, const int item
     for (int c = 0; c < NC; ++c) pj[c] = acc_t{0, 0, 0, 0};
   };
   // projections of atoms g0 .. g0 + 3 from the rows of tile t
-  auto project = [&](int g0, int t, const Tile& u) {
+  auto load_p = [&](int g0, int t, T (&b)[4][CV]) {
     const int g = g0 + cl / 4;
     const bool in = g < np;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      T b[CV];
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int v = 0; v < CV; ++v) {
         const T e = val[((static_cast<int64_t>(in ? g : 0) * NT + t) * CV + v) * 64 + cl % 4 * 16 + NlMma<T>::row(i, q)];
-        b[v] = in ? e : T(0);
+        b[i][v] = in ? e : T(0);
       }
+  };
+  auto project = [&](const T (&b)[4][CV], const Tile& u) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
-        pj[c] = NlMma<T>::run(u.y[c][i], b[0], pj[c]);
-        if constexpr (CPLX) pj[c] = NlMma<T>::run(nl_rot(u.y[c][i], lane), b[1], pj[c]);
+        pj[c] = NlMma<T>::run(u.y[c][i], b[i][0], pj[c]);
+        if constexpr (CPLX) pj[c] = NlMma<T>::run(nl_rot(u.y[c][i], lane), b[i][1], pj[c]);
       }
-    }
   };
   const gptr<T> part = to_global(static_cast<T*>(a.part));
   // accumulator rows are columns of Y, its columns (lane % 16) atom and projector
@@ -395,15 +401,27 @@ __device__ __forceinline__ void nl_update_item(const NlUpdate& a, const int item
       }
   };
   Tile ta, tb;
+  // TOGETHER: the projector values of a tile are requested at once (past the
+  // cell's last atom: its first one's), not one atom after the other
   auto step = [&](int t, Tile& u) {
+    T cv[4][CV], b[4][CV];
+    if constexpr (TOGETHER) {
+#pragma unroll
+      for (int g = 0; g < 4; ++g) load_c(g < np ? g : 0, t, cv[g]);
+      load_p(0, t, b);
+    }
 #pragma unroll
     for (int g = 0; g < 4; ++g)
-      if (g < np) add(g, t, hb[g], u);
+      if (g < np) {
+        if constexpr (!TOGETHER) load_c(g, t, cv[0]);
+        add(cv[TOGETHER ? g : 0], hb[g], u);
+      }
 #pragma unroll 1
     for (int g = 4; g < np; ++g) {
-      T h[NC];
+      T h[NC], c1[CV];
       load_h(g, h);
-      add(g, t, h, u);
+      load_c(g, t, c1);
+      add(c1, h, u);
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -412,7 +430,10 @@ __device__ __forceinline__ void nl_update_item(const NlUpdate& a, const int item
         for (int c = 0; c < NC; ++c)
           if (ok[c]) Y[u.off[i] * ld + col[c]] = u.y[c][i];
       }
-    if (a.part) project(0, t, u);
+    if (a.part) {
+      if constexpr (!TOGETHER) load_p(0, t, b);
+      project(b, u);
+    }
   };
   clear();
   const int t0 = NT * part_z / parts, t1 = NT * (part_z + 1) / parts;
@@ -432,8 +453,10 @@ __device__ __forceinline__ void nl_update_item(const NlUpdate& a, const int item
     clear();
 #pragma unroll 1
     for (int t = 0; t < NT; ++t) {
+      T b[4][CV];
       load(t, ta);
-      project(g0, t, ta);
+      load_p(g0, t, b);
+      project(b, ta);
     }
     put(g0);
   }
@@ -457,7 +480,7 @@ __global__ void __launch_bounds__(256, 4) nl_update_kernel(const NlUpdate a) {
   __shared__ int32_t noff[(P * P * P + 15) / 16 * 16];
   nl_node_offsets<P>(a.nc, noff);
   const int item = __builtin_amdgcn_readfirstlane(blockIdx.x * kNlCells + threadIdx.x / 64);
-  if (item < a.ncells) nl_update_item<P, T, CPLX>(a, item, blockIdx.y, noff, blockIdx.z, gridDim.z);
+  if (item < a.ncells) nl_update_item<P, T, CPLX, !(CPLX && sizeof(T) == 8)>(a, item, blockIdx.y, noff, blockIdx.z, gridDim.z);
 }
 
 // The update of many problems (batched filter): descriptors in device memory.
@@ -466,12 +489,12 @@ __global__ void __launch_bounds__(256, 4)
 nl_update_batched_kernel(const NlUpdate* __restrict__ d, const int64_t* __restrict__ cell_off, const int nprob) {
   __shared__ int32_t noff[(P * P * P + 15) / 16 * 16];
   const int q = __builtin_amdgcn_readfirstlane(problem_of(cell_off, nprob, blockIdx.x));
-  const NlUpdate& a = d[q];
+  const NlUpdate a = d[q];
   if (static_cast<int>(blockIdx.y) * 16 * kNlGroups >= a.nreal) return;
   nl_node_offsets<P>(a.nc, noff);
   const int item =
       __builtin_amdgcn_readfirstlane(static_cast<int>(blockIdx.x - cell_off[q]) * kNlCells + threadIdx.x / 64);
-  if (item < a.ncells) nl_update_item<P, T, CPLX>(a, item, blockIdx.y, noff);
+  if (item < a.ncells) nl_update_item<P, T, CPLX, false>(a, item, blockIdx.y, noff);
 }
 
 // hP[atom][m] = h sum over the atom's pairs of their partial projections, 64
