@@ -474,14 +474,17 @@ int chfsi_scf_kpoints(chfsi_ctx* ctx, int32_t nk, chfsi_op* const* ops, void* co
  * operators must share the context, the order p and the real/complex type;
  * prec is F64, F32 (real) or C128, C64 (complex).  Column blocks of `block`
  * columns (<= 0: all) of every problem are filtered together: each
- * Chebyshev step of a round is ONE launch of a persistent kernel whose work
- * list concatenates every problem's (cell, column tile) items; the per-problem
- * arguments and recurrence scalars come from device tables.  use_graph != 0
+ * Chebyshev step of a round is one launch of the tensor-product kernel over
+ * all problems, and two of the nonlocal kernels where there are projectors; if
+ * an operator has cell matrices of its own, one launch of a persistent kernel
+ * whose work list concatenates every problem's (cell, column tile) items.  The
+ * per-problem arguments and recurrence scalars come from device tables.  use_graph != 0
  * captures the whole sequence into a hipGraph (kept in the context and
  * replayed while the operators, buffers and shapes stay the same).  Grid
- * shape from chfsi_autotune() when tuned, else one workgroup per item.
- * Results equal chfsi_filter() on each block up to the order of the atomic
- * assembly.  Asynchronous. */
+ * shape of the persistent kernel from chfsi_autotune() when tuned, else one
+ * workgroup per item.  Results equal chfsi_filter() on each block up to the
+ * order of sums (on the tensor-product path: of the projections).
+ * Asynchronous. */
 int chfsi_filter_batched(chfsi_ctx* ctx, int32_t n, chfsi_op* const* ops, void* const* X, const int64_t* ncols,
                          const int64_t* ld, int32_t m, const double* a, const double* b, const double* aL,
                          int32_t prec, int32_t block, int32_t use_graph);
@@ -507,8 +510,9 @@ int chfsi_solve_batched(chfsi_ctx* ctx, int32_t n, chfsi_op* const* ops, const c
                         chfsi_stats* stats, int32_t use_graph);
 
 /* ---- autotuner of the batched launch ----------------------------------------
- * Times the batched filter on a synthetic batch of four uneven boxes of order
- * p with `block` columns over launch shapes: the work item of the cell kernel
+ * Times the batched filter by the dense cell kernel (the one that batches with
+ * per-cell matrices run) on a synthetic batch of four uneven boxes of order p
+ * with `block` columns over launch shapes: the work item of the cell kernel
  * (a cell by 64 columns, on 4 waves, or on 2 waves where real FP32 gives each
  * wave all 64 columns; or a cell by 32 columns on half the waves) times the
  * grid (one workgroup per item, reported as grid_per_cu = 0, or a persistent
@@ -574,13 +578,15 @@ int chfsi_initial_block(chfsi_op* op, chfsi_mlp* net, uint64_t seed, void* X, in
 
 /* ---- deterministic assembly ----------------------------------------------
  * Section 4.3 assembles the cell products Y^c into the global vector (the
- * scatter of Eq. celldgemm); the default path adds them with hardware
- * atomics, so the order in which the up to 8 cells sharing a node add into
- * it depends on workgroup timing and the result can differ from run to run
- * in the last bits.  chfsi_set_deterministic(ctx, 1) runs every H~.X of the
- * context (chfsi_apply, chfsi_apply_noalloc, the filter, the solvers, and the
- * batched filter and solve, which then run problem by problem) colour class
- * by colour class: along each axis the cells take colours 0, 1, 0, 1, ...
+ * scatter of Eq. celldgemm).  The tensor-product kernel computes every node
+ * once, in a fixed order.  The dense cell kernel (BF16 products, per-cell
+ * matrices, and blocks with planes of 2 GB or more) adds with hardware atomics,
+ * so the order in which the up to 8 cells sharing a node add into it depends
+ * on workgroup timing and the result can differ from run to run in the last
+ * bits.  chfsi_set_deterministic(ctx, 1) runs the dense kernel of every H~.X of
+ * the context (chfsi_apply, chfsi_apply_noalloc, the filter, the solvers; the
+ * batched filter and solve then run problem by problem) colour class by colour
+ * class: along each axis the cells take colours 0, 1, 0, 1, ...
  * (and 2 for the last cell of an odd side), a class is a triple of axis
  * colours, no two cells of one class share a node, and the classes run in a
  * fixed order, one launch each (8 launches per H~.X for an even number of
@@ -600,11 +606,13 @@ int chfsi_initial_block(chfsi_op* op, chfsi_mlp* net, uint64_t seed, void* X, in
 int chfsi_set_deterministic(chfsi_ctx* ctx, int32_t enable);
 
 /* ---- kernel timing ---------------------------------------------------------
- * When enabled, the library brackets every launch of the cell H~.X kernel
- * with HIP events on the context stream.  chfsi_kernel_time() waits for the
- * stream and returns the summed duration (ms), the number of launches and the
- * summed algorithmic flops of those launches since the last reset (reset != 0
- * clears the counters after reading). */
+ * When enabled, the library brackets every H~.X (the cell kernel; the
+ * tensor-product kernel with the nonlocal update behind it) with HIP events on
+ * the context stream.  chfsi_kernel_time() waits for the stream and returns the
+ * summed duration (ms), the number of products and their summed algorithmic
+ * flops since the last reset (reset != 0 clears the counters after reading).
+ * The flops are those of the dense cell products, in whatever form they are
+ * made: the tensor-product kernel does about a twelfth of them at p = 6. */
 int chfsi_set_timing(chfsi_ctx* ctx, int32_t enable);
 int chfsi_kernel_time(chfsi_ctx* ctx, double* total_ms, int64_t* launches, double* flops, int32_t reset);
 

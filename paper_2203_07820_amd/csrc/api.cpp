@@ -268,9 +268,9 @@ double hx_flops(const chfsi_op* op, int64_t ncols) {
   return fl;
 }
 
-// the part of hx_flops that the cell kernel itself does: the cell products
-// and C (h P) per (cell, atom) pair, without the projection P = C^H X, which
-// the nonlocal kernels do before it
+// the part of hx_flops that the timed launches do: the cell products (counted
+// as the dense ones they stand for) and C (h P) per (cell, atom) pair, without
+// the projection P = C^H X
 double cell_kernel_flops(const chfsi_op* op, int64_t ncols) {
   const HostTables& t = op->t;
   const double cfl = t.cplx ? 4.0 : 1.0;
@@ -379,16 +379,16 @@ int hx_step(chfsi_op* op, int prec, const void* Xk, int64_t ldx, const void* Xp,
   else
     CHECK(launch_hx_cells(op, make_hx(op, prec, Xk, ldx, Xp, ldp, T, ldt, ncols, alpha, c, beta, zero_prev, hP, ldhp),
                           prec));
-  if (ctx->timing) {
-    HIP_TRY(ctx, hipEventRecord(e1, ctx->stream));
-    ctx->pending.emplace_back(e0, e1);
-    ctx->pending_flops.push_back(cell_kernel_flops(op, ncols));
-  }
   if (tensor && t.has_proj) {
     void* pp = nullptr;
     if (project_next)
       CHECK(ws_get(ctx, WS_NLPAIR, static_cast<size_t>(op->nown_pairs) * 4 * ldhp * (single ? 4 : 8), &pp));
     HIP_TRY(ctx, launch_nl_update(make_update(op, prec, T, ldt, ncols, alpha, hP, ldhp, pp), t.p, prec, ctx->stream));
+  }
+  if (ctx->timing) {
+    HIP_TRY(ctx, hipEventRecord(e1, ctx->stream));
+    ctx->pending.emplace_back(e0, e1);
+    ctx->pending_flops.push_back(cell_kernel_flops(op, ncols));
   }
   return 0;
 }
@@ -1219,11 +1219,6 @@ int batched_tensor_filter(chfsi_ctx* ctx, const std::vector<BItem>& items, int m
           HIP_TRY(ctx, hipEventRecord(e0, ctx->stream));
         }
         HIP_TRY(ctx, launch_tensor_batched(tb, prec, ctx->stream));
-        if (timed) {
-          HIP_TRY(ctx, hipEventRecord(e1, ctx->stream));
-          ctx->pending.emplace_back(e0, e1);
-          ctx->pending_flops.push_back(R.flops);
-        }
         if (R.nl > 0) {
           NlUpdateBatch b;
           b.descs = dtab + up_at + at * sizeof(NlUpdate);
@@ -1236,6 +1231,11 @@ int batched_tensor_filter(chfsi_ctx* ctx, const std::vector<BItem>& items, int m
           b.max_ldhp = R.max_ldhp;
           b.project = st < m;
           HIP_TRY(ctx, launch_nl_update_batched(b, items[0].op->t.p, prec, ctx->stream));
+        }
+        if (timed) {
+          HIP_TRY(ctx, hipEventRecord(e1, ctx->stream));
+          ctx->pending.emplace_back(e0, e1);
+          ctx->pending_flops.push_back(R.flops);
         }
       }
       if (!(in_place && m % 2 == 0))

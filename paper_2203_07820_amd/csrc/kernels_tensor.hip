@@ -32,6 +32,12 @@
 //   At a plane's own step they add the potential and -beta X_{k-1}.  Complete
 //   planes are stored, in place over X_{k-1} in the filter.
 // The nonlocal term is added by nl_update_kernel.
+// Bound by memory: on 24^3 cells, p = 6, 128 columns, FP64, a filter step moves
+// 11.3 GB (9.2 GB needed) in 3.03 ms, where a three-stream add over as much
+// runs at 5.5 TB/s; 7.9 ms by the dense cell kernel, which moved 17.5 GB.  The
+// first step (no X_{k-1}): 2.56 ms; FP32 1.32 ms (5.1 dense); 12^3 cells, p = 5,
+// 160 columns: 0.257 ms (0.76 dense); 20^3 cells, p = 5, complex FP64: 1.98 ms
+// (7.1 dense).
 // LDS is double buffered with one barrier per plane; a chunk starts with the
 // cell below it, whose top plane it shares.
 #include <hip/hip_runtime.h>
