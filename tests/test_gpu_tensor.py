@@ -195,3 +195,27 @@ def test_bounds_refuses_a_zero_start(ctx):
 def test_narrow_projection(ctx, ncols, k):
     for single in (False, True):
         _run(ctx, 3, 5, 3, k, ncols, ncols + 1, single, 2)
+
+
+# planes of 2 GB go to the dense kernel (32-bit offsets in a plane), smaller
+# ones to the tensor-product kernel: 4^2 nodes x 2^24 doubles, and one less
+@pytest.mark.parametrize("ld", [2 ** 24 - 1, 2 ** 24])
+def test_plane_limit(ctx, ld):
+    s = workloads.small_system(2, 2, 1, seed=2, has_proj=True)
+    op = lib.Operator(ctx, s)
+    H = fe.assemble(fe.build_operator(s))
+    X = workloads.start_block(op.M, 3, seed=7)
+    buf = torch.zeros(op.M, ld, dtype=torch.float64, device="cuda")
+    out = torch.full_like(buf, 5.0)
+    buf[:, :3] = torch.from_numpy(X).cuda()
+    for call in (ctx.lib.chfsi_apply, ctx.lib.chfsi_apply_noalloc):
+        ctx.check(call(op.h, lib._tptr(buf), lib._tptr(out), 3, ld, lib.F64))
+        torch.cuda.synchronize()
+        assert _relerr(out[:, :3].cpu().numpy(), H @ X) < 1e-12
+        assert bool((out[:, 3:5] == 5).all()) and bool((out[:, -2:] == 5).all())
+        out[:, :3] = 5.0
+    b = float(abs(H).sum(axis=1).max())
+    want = ochfsi.cheb_filter(lambda v: H @ v, X, 3, 0.3 * b, b, -1.0)
+    ctx.check(ctx.lib.chfsi_filter(op.h, lib._tptr(buf), 3, ld, 3, 0.3 * b, b, -1.0, lib.F64, 0))
+    torch.cuda.synchronize()
+    assert _relerr(buf[:, :3].cpu().numpy(), want) < 1e-11
