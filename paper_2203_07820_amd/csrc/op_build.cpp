@@ -392,16 +392,21 @@ std::string build_tables(const chfsi_system& sys, HostTables& t) {
   // atom-major list are written to their places.
   struct Holder { int64_t cell; int lid; };
   Holder hold[8];
-  auto holders = [&](int64_t node) {   // the first one is the owner
+  std::vector<int> cell1(n), loc1(n);   // cell and local index of a 1D node
+  for (int i = 0; i < n; ++i) {
+    cell1[i] = i / p;
+    loc1[i] = i % p;
+  }
+  auto holders = [&](int32_t node) {   // the first one is the owner
+    const uint32_t un = static_cast<uint32_t>(n), v = static_cast<uint32_t>(node), vy = v / un;
+    const uint32_t i1[3] = {v - vy * un, vy % un, vy / un};
     int c[3][2], a[3][2], cnt[3];
-    int64_t v = node;
-    for (int d = 0; d < 3; ++d, v /= n) {
-      const int i1 = static_cast<int>(v % n);
-      c[d][0] = i1 / p;
-      a[d][0] = i1 % p;
+    for (int d = 0; d < 3; ++d) {
+      c[d][0] = cell1[i1[d]];
+      a[d][0] = loc1[i1[d]];
       cnt[d] = 1;
-      if (i1 % p == 0) {
-        c[d][1] = (i1 / p - 1 + nc) % nc;
+      if (a[d][0] == 0) {
+        c[d][1] = (c[d][0] - 1 + nc) % nc;
         a[d][1] = p;
         cnt[d] = 2;
       }
@@ -465,8 +470,7 @@ std::string build_tables(const chfsi_system& sys, HostTables& t) {
     t.atom_pair_ptr.push_back(static_cast<int32_t>(t.atom_pair.size()));
     for (int64_t e = t.atom_ptr[at]; e < t.atom_ptr[at + 1]; ++e) {
       const double* v = &t.atom_val[e * vw];
-      const int64_t node = t.atom_node[e];
-      const int k = holders(node);
+      const int k = holders(t.atom_node[e]);
       const double inv_mult = 1.0 / k;
       for (int u = 0; u < k; ++u) {
         const int lid = hold[u].lid;
