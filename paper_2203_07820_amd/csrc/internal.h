@@ -292,8 +292,33 @@ hipError_t launch_convert(void* dst, int64_t ldd, int dprec, const void* src, in
                           int64_t rows, int64_t cols, hipStream_t s);
 
 // Dense FP64 kernels on real views.
-// Lower-triangular Gram G = X^T Y (n x n, real view) -> partial buffers then
-// reduced into G (row-major, ldg), upper triangle mirrored.
+// Lower-triangular Gram G = X^T Y (n x n, real view) by blocks of kGramBlock
+// columns and chunks of rows -> partial buffers, then reduced into G
+// (row-major, ldg); entries above the 16 x 16 tiles of the diagonal are left as
+// they are.
+constexpr int kGramBlock = 64;
+constexpr int kGramWaves = 4096;  // waves of a product: two rounds of two per SIMD
+inline int gram_blocks(int n) {
+  const int nb = (n + kGramBlock - 1) / kGramBlock;
+  return nb * (nb + 1) / 2;
+}
+// Row chunks of a product: about kGramWaves waves in all, at least 256 rows per
+// chunk, and few enough rows that a chunk of the widest operand (ld doubles per
+// row) spans less than 2^31 bytes (32-bit buffer offsets).  The count is rounded
+// down, to end with full rounds, except in single precision, where a chunk's
+// rows are also the length of an FP32 sum: there it is rounded up, so that the
+// sums of a wide product, of few chunks, are no longer than its share of rows.
+inline int gram_chunks(int64_t M, int n, int64_t ld, bool single) {
+  const int blocks = gram_blocks(n);
+  int64_t ch = single ? (kGramWaves + blocks - 1) / blocks : kGramWaves / blocks;
+  const int64_t max_ch = (M + 255) / 256;
+  if (ch > max_ch) ch = max_ch;
+  const int64_t max_rows = ((int64_t{1} << 31) - 1) / (8 * (ld > 0 ? ld : 1)) - 16;
+  const int64_t min_ch = max_rows > 0 ? (M + max_rows - 1) / max_rows : M;
+  if (ch < min_ch) ch = min_ch;
+  if (ch < 1) ch = 1;
+  return static_cast<int>(ch);
+}
 size_t gram_partial_bytes(int64_t M, int n, int64_t ld);
 // X / Y may point offx / offy columns into their rows (a column slice of a
 // block whose rows hold ldx / ldy values); offx + n <= ldx, offy + n <= ldy.
@@ -320,7 +345,6 @@ hipError_t launch_resid(const double* HX, int64_t ldh, const double* X, int64_t 
 // dot partial sums of two real-view vectors of length n: partial[block]
 int dot_blocks();
 hipError_t launch_dot(const double* x, const double* y, int64_t n, double* partial, hipStream_t s);
-// y = a*x + b*y over n reals
 // One Lanczos step's vector work with its scalars on the device (part1, part2:
 // dot_blocks() partial sums each):
 // scale: *bb = sum(part1), v = f / sqrt(*bb) (0 where that is not positive);
@@ -331,6 +355,7 @@ hipError_t launch_lanczos_orth(const double* bb, const double* vprev, const doub
                                double* part2, hipStream_t s);
 hipError_t launch_lanczos_close(const double* part2, double* alpha, const double* v, double* f, int64_t n,
                                 double* part1, hipStream_t s);
+// y = a*x + b*y over n reals
 hipError_t launch_axpby(double a, const double* x, double b, double* y, int64_t n, hipStream_t s);
 // small matrix helpers (n x n)
 hipError_t launch_transpose(const double* in, double* out, int n, hipStream_t s);

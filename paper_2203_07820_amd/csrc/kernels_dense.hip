@@ -59,8 +59,7 @@ template <> struct Mfma<float> {
 // (136 of the 192 tiles that 128 x 128 workgroups multiplied):
 // 5.9 -> 4.3 ms, 77 % of the cycles multiplying; on 216,000 x 160, 0.384 ->
 // 0.166 ms.  (2048 waves: 0.177 ms there; 8192: 0.170 ms and a longer sum.)
-constexpr int kGB = 64;          // columns of a block
-constexpr int kGramWaves = 4096;  // waves of a product: two rounds of two per SIMD
+constexpr int kGB = kGramBlock;  // columns of a block
 constexpr int kGramStages = 3;   // register stages (loads GS - 1 steps ahead)
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* p, uint32_t bytes) {
@@ -705,32 +704,14 @@ unsigned blocks_for(int64_t total, int per = 256) {
   return static_cast<unsigned>((total + per - 1) / per);
 }
 
-// Row chunks of the Gram products: about 4096 waves in all (two rounds of two
-// per SIMD), at least 256 rows per chunk, and few enough rows that a chunk of
-// the widest operand (ld doubles per row) spans less than 2^31 bytes (32-bit
-// buffer offsets).
-int gram_blocks(int n) {
-  const int nb = (n + kGB - 1) / kGB;
-  return nb * (nb + 1) / 2;
-}
-int gram_chunks(int64_t M, int n, int64_t ld) {
-  int64_t ch = kGramWaves / gram_blocks(n);
-  const int64_t max_ch = (M + 255) / 256;
-  if (ch > max_ch) ch = max_ch;
-  const int64_t max_rows = ((int64_t{1} << 31) - 1) / (8 * (ld > 0 ? ld : 1)) - 16;
-  const int64_t min_ch = max_rows > 0 ? (M + max_rows - 1) / max_rows : M;
-  if (ch < min_ch) ch = min_ch;
-  if (ch < 1) ch = 1;
-  return static_cast<int>(ch);
-}
-
 }  // namespace
 
 size_t gram_partial_bytes(int64_t M, int n, int64_t ld) {
-  // what the widest of all products of up to n columns takes
+  // what the widest of all products of up to n columns takes, in either
+  // precision (single precision has the more chunks)
   int64_t blocks = 0;
   for (int w = kGB; w < n + kGB; w += kGB)
-    blocks = std::max(blocks, static_cast<int64_t>(gram_chunks(M, w, ld)) * gram_blocks(w));
+    blocks = std::max(blocks, static_cast<int64_t>(gram_chunks(M, w, ld, true)) * gram_blocks(w));
   return static_cast<size_t>(blocks) * kGB * kGB * sizeof(double);
 }
 
@@ -739,7 +720,7 @@ hipError_t gram_t(const T* X, int64_t ldx, const T* Y, int64_t ldy, int64_t M, i
                   double* G, int64_t ldg, hipStream_t s, int64_t offx, int64_t offy) {
   if (offx < 0 || offy < 0 || offx + n > ldx || offy + n > ldy) return hipErrorInvalidValue;
   if (n <= 0) return hipSuccess;
-  int nch = gram_chunks(M, n, ldx > ldy ? ldx : ldy);
+  int nch = gram_chunks(M, n, ldx > ldy ? ldx : ldy, sizeof(T) == 4);
   GramArgs<T> a;
   a.X = X;
   a.Y = Y;
