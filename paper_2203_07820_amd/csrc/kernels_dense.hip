@@ -209,24 +209,29 @@ gram_kernel(const GramArgs<T> a) {
 
 // G = sums of the chunks' blocks, 64 entries per workgroup (one row of a
 // block): 4 waves take every 4th chunk, their sums are added in a fixed order.
-// Entries above the 16 x 16 tiles of the diagonal are left as they are.
+// Entries above the 16 x 16 tiles of the diagonal are left as they are.  A grid
+// holds 65535 in y: the blocks beyond (from 23,105 columns on) are taken by the
+// same workgroups in turn.
 __global__ void __launch_bounds__(256)
 gram_reduce_kernel(const double* __restrict__ part, int nchunks, int nblk, int n, double* __restrict__ G, int64_t ldg) {
   __shared__ double red[4][64];
-  const int t = blockIdx.y, r = blockIdx.x, c = threadIdx.x % 64, wave = threadIdx.x / 64;
-  const int I = tri_row(t), J = t - I * (I + 1) / 2;
-  const int i = I * kGB + r, j = J * kGB + c;
-  double s = 0.0;
-  if (i < n && j / 16 <= i / 16) {
-    const double* p = part + (static_cast<int64_t>(t) * kGB + r) * kGB + c;
-    const int64_t step = static_cast<int64_t>(nblk) * kGB * kGB;
+  const int r = blockIdx.x, c = threadIdx.x % 64, wave = threadIdx.x / 64;
+  for (int t = blockIdx.y; t < nblk; t += gridDim.y) {
+    const int I = tri_row(t), J = t - I * (I + 1) / 2;
+    const int i = I * kGB + r, j = J * kGB + c;
+    double s = 0.0;
+    if (i < n && j / 16 <= i / 16) {
+      const double* p = part + (static_cast<int64_t>(t) * kGB + r) * kGB + c;
+      const int64_t step = static_cast<int64_t>(nblk) * kGB * kGB;
 #pragma unroll 8
-    for (int q = wave; q < nchunks; q += 4) s += p[q * step];
+      for (int q = wave; q < nchunks; q += 4) s += p[q * step];
+    }
+    red[wave][c] = s;
+    __syncthreads();
+    if (wave == 0 && i < n && j < n && j / 16 <= i / 16)
+      G[static_cast<int64_t>(i) * ldg + j] = ((s + red[1][c]) + red[2][c]) + red[3][c];
+    __syncthreads();
   }
-  red[wave][c] = s;
-  __syncthreads();
-  if (wave == 0 && i < n && j < n && j / 16 <= i / 16)
-    G[static_cast<int64_t>(i) * ldg + j] = ((s + red[1][c]) + red[2][c]) + red[3][c];
 }
 
 // Real symmetric result from the lower entries: S[i][j] = G[max][min].
@@ -738,7 +743,8 @@ hipError_t gram_t(const T* X, int64_t ldx, const T* Y, int64_t ldy, int64_t M, i
   if (nwg > 0x7fffffff) return hipErrorInvalidValue;
   if (nwg > 0)
     hipLaunchKernelGGL((gram_kernel<T, kGramStages>), dim3(static_cast<unsigned>(nwg)), dim3(64), 0, s, a);
-  hipLaunchKernelGGL(gram_reduce_kernel, dim3(kGB, a.nblk), dim3(256), 0, s, partial, nch, a.nblk, n, G, ldg);
+  hipLaunchKernelGGL(gram_reduce_kernel, dim3(kGB, std::min(a.nblk, 65535)), dim3(256), 0, s, partial, nch, a.nblk, n,
+                     G, ldg);
   return hipGetLastError();
 }
 
