@@ -580,10 +580,12 @@ int chfsi_initial_block(chfsi_op* op, chfsi_mlp* net, uint64_t seed, void* X, in
  * Section 4.3 assembles the cell products Y^c into the global vector (the
  * scatter of Eq. celldgemm).  The tensor-product kernel computes every node
  * once, in a fixed order.  The dense cell kernel (BF16 products, per-cell
- * matrices, and blocks with planes of 2 GB or more) adds with hardware atomics,
+ * matrices, blocks with planes of 2 GB or more, and single products with
+ * projectors on small meshes of order 2 and 3) adds with hardware atomics,
  * so the order in which the up to 8 cells sharing a node add into it depends
  * on workgroup timing and the result can differ from run to run in the last
- * bits.  chfsi_set_deterministic(ctx, 1) runs the dense kernel of every H~.X of
+ * bits.  chfsi_set_deterministic(ctx, 1) takes the tensor-product kernel for
+ * those small products too and runs the dense kernel of every other H~.X of
  * the context (chfsi_apply, chfsi_apply_noalloc, the filter, the solvers; the
  * batched filter and solve then run problem by problem) colour class by colour
  * class: along each axis the cells take colours 0, 1, 0, 1, ...

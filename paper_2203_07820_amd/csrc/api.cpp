@@ -290,6 +290,29 @@ bool tensor_path(const chfsi_op* op, int prec, int64_t ldmax) {
   return static_cast<double>(n) * n * ldmax * prec_bytes(prec) < 2147483648.0;
 }
 
+// The same for a product on its own.  A filter's step leaves the next one's
+// projections behind; a single product with projectors only pays for the
+// nonlocal update after the tensor-product kernel, 5-6 us, and on a small mesh
+// of cells of order 2 or 3 the dense kernel, which adds the term itself, takes no
+// longer than the tensor-product kernel alone.  Those products stay with it,
+// except in deterministic mode, where it would need a launch per colour class.
+// Whole products, dense and tensor-product: 33 columns, FP64, 4^3 cells p = 2
+// 20.2 and 22.7 us, 4^3 cells p = 3 23.0 and 26.6, 8^3 36.0 and 41.3; 128 columns,
+// 8^3 67.5 and 53.3.  The line is by cells x columns x operations per entry (4 in
+// complex data, half in single precision).  Up to 5^3 cells: complex FP64, p = 3,
+// 64 columns (32,000) 36.5 and 39.9, 128 (64,000) 50.7 and 51.3.  Beyond:
+// 6^3 cells, 33 columns (28,512) 42.3 and 44.5, 128 (110,592) 73.7 and 60.6.  Above
+// 6^3 cells only FP64 gains: 8^3, 33 columns, FP32 35.9 and 33.5.  From order 4 on
+// the tensor-product kernel: 2^3 cells, 33 columns, FP64 31.0 and 28.9.
+bool tensor_single(const chfsi_op* op, int prec, int64_t ldmax, int64_t ncols) {
+  if (!tensor_path(op, prec, ldmax)) return false;
+  const HostTables& t = op->t;
+  if (!t.has_proj || t.p > 3 || op->ctx->deterministic) return true;
+  const double work = static_cast<double>(t.E) * ncols * (t.cplx ? 4.0 : 1.0) * (is_single(prec) ? 0.5 : 1.0);
+  if (t.E <= 125) return work > 64000.0;
+  return work > 30000.0 || t.E > (prec == CHFSI_F64 ? 512 : 216);
+}
+
 // T = alpha (H~ Xk - c Xk) - beta Xp through the tensor-product kernel.
 TensorLaunch make_tensor(const chfsi_op* op, int prec, const void* Xk, int64_t ldx, const void* Xp, int64_t ldp,
                          void* T, int64_t ldt, int64_t ncols, double alpha, double c, double beta) {
@@ -344,12 +367,12 @@ NlUpdate make_update(const chfsi_op* op, int prec, void* Y, int64_t ldy, int64_t
 }
 
 // Y = alpha (H~ Xk - c Xk) - beta Xp: stored into T on the tensor-product
-// path (T may be Xp), accumulated into T on the dense one (T must hold 0 on
-// entry).  Xk, Xp, T are in the storage type of prec, logical ld.
+// path (`tensor`; T may be Xp), accumulated into T on the dense one (T must
+// hold 0 on entry).  Xk, Xp, T are in the storage type of prec, logical ld.
 // On the tensor-product path, `projected` says that the projector coefficients
 // of Xk are already in the workspace, and `project_next` leaves those of T
 // there for the next step of a filter.
-int hx_step(chfsi_op* op, int prec, const void* Xk, int64_t ldx, const void* Xp, int64_t ldp, void* T,
+int hx_step(chfsi_op* op, int prec, bool tensor, const void* Xk, int64_t ldx, const void* Xp, int64_t ldp, void* T,
             int64_t ldt, int64_t ncols, double alpha, double c, double beta, bool zero_prev, bool projected = false,
             bool project_next = false) {
   chfsi_ctx* ctx = op->ctx;
@@ -365,7 +388,6 @@ int hx_step(chfsi_op* op, int prec, const void* Xk, int64_t ldx, const void* Xp,
     CHECK(ws_get(ctx, WS_HP, static_cast<size_t>(t.natoms) * 4 * ldhp * eb, &hP));
     if (!projected) CHECK(nl_project(op, prec, Xk, ldx, ncols, part, hP, ldhp));
   }
-  const bool tensor = tensor_path(op, prec, std::max({ldx, ldp, ldt}));
   if (ctx->deterministic) CHECK(build_colours(op));
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (ctx->timing) {
@@ -428,21 +450,21 @@ int filter_block(chfsi_op* op, int prec, void* const R[4], int64_t ncols, const 
   const int sp = storage_of(prec);
   if (tensor_path(op, prec, std::max(ldr[0], ldr[1]))) {
     // two buffers: step i stores over X_{i - 2}, in place
-    CHECK(hx_step(op, prec, R[0], ldr[0], nullptr, ldr[0], R[1], ldr[1], ncols, al[0], c, 0.0, false, false,
+    CHECK(hx_step(op, prec, true, R[0], ldr[0], nullptr, ldr[0], R[1], ldr[1], ncols, al[0], c, 0.0, false, false,
                   m > 1));
     for (int i = 2; i <= m; ++i) {
       const int k = (i - 1) % 2, t = i % 2;
-      CHECK(hx_step(op, prec, R[k], ldr[k], R[t], ldr[t], R[t], ldr[t], ncols, al[i - 1], c, be[i - 1], false,
+      CHECK(hx_step(op, prec, true, R[k], ldr[k], R[t], ldr[t], R[t], ldr[t], ncols, al[i - 1], c, be[i - 1], false,
                     true, i < m));
     }
     *out_idx = m % 2;
     return 0;
   }
   for (int i = 1; i < 4; ++i) HIP_TRY(ctx, launch_fill(R[i], M, ncols * cf, ldr[i] * cf, sp, ctx->stream));
-  CHECK(hx_step(op, prec, R[0], ldr[0], nullptr, ldr[0], R[1], ldr[1], ncols, al[0], c, 0.0, false));
+  CHECK(hx_step(op, prec, false, R[0], ldr[0], nullptr, ldr[0], R[1], ldr[1], ncols, al[0], c, 0.0, false));
   for (int i = 2; i <= m; ++i) {
     const int k = (i - 1) % 4, p = (i - 2) % 4, t = i % 4;
-    CHECK(hx_step(op, prec, R[k], ldr[k], R[p], ldr[p], R[t], ldr[t], ncols, al[i - 1], c, be[i - 1], true));
+    CHECK(hx_step(op, prec, false, R[k], ldr[k], R[p], ldr[p], R[t], ldr[t], ncols, al[i - 1], c, be[i - 1], true));
   }
   *out_idx = m % 4;
   return 0;
@@ -604,8 +626,9 @@ int rayleigh_ritz(chfsi_op* op, const double* X, int64_t ldx, double* Psi, int64
   const int prec = cplx ? CHFSI_C128 : CHFSI_F64;
   void *W, *HPsi;
   CHECK(ws_get(ctx, WS_W, static_cast<size_t>(t.M) * N * 8 * cf, &W));
-  if (!tensor_path(op, prec, std::max(ldx, N))) HIP_TRY(ctx, launch_fill(W, t.M, N * cf, N * cf, prec, ctx->stream));
-  CHECK(hx_step(op, prec, X, ldx, nullptr, 0, W, N, N, 1.0, 0.0, 0.0, false));
+  const bool tensor = tensor_single(op, prec, std::max(ldx, N), N);
+  if (!tensor) HIP_TRY(ctx, launch_fill(W, t.M, N * cf, N * cf, prec, ctx->stream));
+  CHECK(hx_step(op, prec, tensor, X, ldx, nullptr, 0, W, N, N, 1.0, 0.0, 0.0, false));
   double* Hh = nullptr;
   CHECK(gram(op, X, ldx, static_cast<double*>(W), N, N, &Hh));
   void *dinfo, *eig;
@@ -725,8 +748,9 @@ int rrgep_split(chfsi_op* op, double* X, int64_t ldx, int64_t N, int nfr, bool m
     return 0;
   };
   // RRGEP-P needs W = H~ X
-  if (!tensor_path(op, prec, std::max(ldx, N))) HIP_TRY(ctx, launch_fill(W, M, nr, nr, prec, st));
-  CHECK(hx_step(op, prec, X, ldx, nullptr, 0, W, N, N, 1.0, 0.0, 0.0, false));
+  const bool tensor = tensor_single(op, prec, std::max(ldx, N), N);
+  if (!tensor) HIP_TRY(ctx, launch_fill(W, M, nr, nr, prec, st));
+  CHECK(hx_step(op, prec, tensor, X, ldx, nullptr, 0, W, N, N, 1.0, 0.0, 0.0, false));
   float *X32 = nullptr, *W32 = nullptr;
   if (mixed) {
     void *a, *b;
@@ -909,12 +933,12 @@ int do_bounds(chfsi_op* op, int steps, const double* v0_dev, const double* v0_ho
   // f is the start vector, then v = f / |f| ; f = H v - |f| vprev ; alpha = v.f ; f -= alpha v
   std::swap(f, v);
   HIP_TRY(ctx, launch_dot(f, f, nr, part1, ctx->stream));
-  const bool tensor = tensor_path(op, prec, 1);
+  const bool tensor = tensor_single(op, prec, 1, 1);
   for (int k = 0; k < steps; ++k) {
     std::swap(v, vprev);
     HIP_TRY(ctx, launch_lanczos_scale(part1, out + k, f, v, nr, ctx->stream));
     if (!tensor) HIP_TRY(ctx, launch_fill(f, t.M, cf, cf, prec, ctx->stream));
-    CHECK(hx_step(op, prec, v, 1, nullptr, 1, f, 1, 1, 1.0, 0.0, 0.0, false));
+    CHECK(hx_step(op, prec, tensor, v, 1, nullptr, 1, f, 1, 1, 1.0, 0.0, 0.0, false));
     HIP_TRY(ctx, launch_lanczos_orth(out + k, k ? vprev : nullptr, v, f, nr, part2, ctx->stream));
     HIP_TRY(ctx, launch_lanczos_close(part2, out + steps + 1 + k, v, f, nr, part1, ctx->stream));
   }
@@ -2098,8 +2122,9 @@ int chfsi_apply(chfsi_op* op, const void* X, void* Y, int64_t ncols, int64_t ld,
   if (X == Y) return fail(ctx, CHFSI_EINVAL, "X and Y must not overlap");
   const int cf = op->t.cplx ? 2 : 1;
   const int sp = storage_of(prec);
-  if (!tensor_path(op, prec, ld)) HIP_TRY(ctx, launch_fill(Y, op->t.M, ncols * cf, ld * cf, sp, ctx->stream));
-  return hx_step(op, prec, X, ld, nullptr, ld, Y, ld, ncols, 1.0, 0.0, 0.0, false);
+  const bool tensor = tensor_single(op, prec, ld, ncols);
+  if (!tensor) HIP_TRY(ctx, launch_fill(Y, op->t.M, ncols * cf, ld * cf, sp, ctx->stream));
+  return hx_step(op, prec, tensor, X, ld, nullptr, ld, Y, ld, ncols, 1.0, 0.0, 0.0, false);
 }
 
 int chfsi_apply_noalloc(chfsi_op* op, const void* X, void* Y, int64_t ncols, int64_t ld, int32_t prec) {
@@ -2123,7 +2148,7 @@ int chfsi_apply_noalloc(chfsi_op* op, const void* X, void* Y, int64_t ncols, int
                     std::to_string(ncols) + " columns; the fixed scratch holds " + std::to_string(kScratchBytes) +
                     " (use fewer columns per call, or chfsi_apply)");
   if (t.has_proj && !ctx->scratch) return fail(ctx, CHFSI_EHIP, "fixed scratch unavailable: " + ctx->scratch_err);
-  const bool tensor = tensor_path(op, prec, ld);
+  const bool tensor = tensor_single(op, prec, ld, ncols);
   if (!tensor) HIP_TRY(ctx, launch_fill(Y, t.M, ncols * cf, ld * cf, sp, ctx->stream));
   void* hP = nullptr;
   if (t.has_proj) {
@@ -2911,7 +2936,7 @@ int subspace_small_batched(chfsi_ctx* ctx, const std::vector<int>& idx, chfsi_op
     const int prec = op->t.cplx ? CHFSI_C128 : CHFSI_F64;
     double* W = at(oW[k]);
     HIP_TRY(ctx, launch_fill(W, op->t.M, Nq * cf, Nq * cf, prec, ctx->stream));
-    CHECK(hx_step(op, prec, X2, Nq, nullptr, 0, W, Nq, Nq, 1.0, 0.0, 0.0, false));
+    CHECK(hx_step(op, prec, tensor_single(op, prec, Nq, Nq), X2, Nq, nullptr, 0, W, Nq, Nq, 1.0, 0.0, 0.0, false));
     double* Hh = at(oH[k]);
     CHECK(gram(op, X2, Nq, W, Nq, Nq, &Hh));
   }

@@ -1,8 +1,9 @@
 // Cell-wise H~.X on gfx950 (DFT-FE 1.0, Section 4.3, Eq. celldgemm and
 // Algorithm 4), fused with one step of the scaled Chebyshev recurrence
 // (Section 3.1), by the dense cell matrix: for BF16 products, whose rounding is
-// defined on its entries, per-cell matrices (quadrature potential) and blocks
-// with planes of 2 GB or more.  Everything else takes the tensor-product kernel
+// defined on its entries, per-cell matrices (quadrature potential), blocks
+// with planes of 2 GB or more, and single products on small meshes of order 2
+// and 3.  Everything else takes the tensor-product kernel
 // (kernels_tensor.hip), 2.6 times faster in FP64 at p = 6.
 //
 // One workgroup owns one hexahedral cell and a 64-wide tile of columns.  It

@@ -608,7 +608,10 @@ int64_t ts_pack(const TensorLaunch& L, double share, TsArgs<T>& a) {
 // node (3 cells against 2 at p = 6, 24^3 cells, 128 columns: 2.56 against
 // 2.71 ms in FP64, 1.31 against 1.53 ms in FP32), as far as the LDS and, for
 // complex p = 6, the registers allow; two cells where the wide tile would
-// leave more than an eighth of its cells beyond the mesh.
+// leave more than an eighth of its cells beyond the mesh, and in launches of
+// their own that are short of workgroups (launch_tensor_hx): without projectors,
+// 3^3 cells, p = 3, 33 columns, 9.8 against 11.6 us in single complex precision,
+// 7.8 against 8.6 in FP64.
 constexpr int wide_tile(int p, bool cplx) { return p <= 3 ? 4 : (p <= 5 || (p == 6 && !cplx) ? 3 : 2); }
 inline bool use_wide(const int* nc, int n, int wide) {
   double w = 0, two = 0;
@@ -685,7 +688,11 @@ void pack_tensor_tables(int p, const double* K1, const double* S1, const double*
 
 hipError_t launch_tensor_hx(const TensorLaunch& L, int prec, hipStream_t s) {
   if (!ts_valid(L.p, prec)) return hipErrorInvalidValue;
-  return ts_dispatch(L.p, prec, tensor_batch_wide(L.p, prec, {L.nc}), [&](auto tag) {
+  // a launch whose two-cell tiles, one cell high, all run at once is as long as
+  // one of them: the wide ones, with more work in each, only lengthen it
+  const int ncol = prec == CHFSI_F64 || prec == CHFSI_C128 ? kL : 2 * kL;
+  const bool few = static_cast<int64_t>((L.ncols + ncol - 1) / ncol) * L.nc * L.nc * ((L.nc + 1) / 2) <= L.ncu;
+  return ts_dispatch(L.p, prec, !few && tensor_batch_wide(L.p, prec, {L.nc}), [&](auto tag) {
     typedef decltype(tag) Tag;
     TsArgs<typename Tag::real> a;
     const int64_t nblk = Tag::pack(L, 1.0, a);
