@@ -45,42 +45,58 @@ int upload(chfsi_op* op, const std::vector<T>& v, T** out) {
   return 0;
 }
 
-// A table in double and in single precision.  Large ones (all of them multiples
-// of 64 entries) are rounded on the device: their second copy over the host
-// link and the host's conversion were a fifth of the operator build.
+// Several index tables in one allocation and one copy: on a small operator each
+// of its own costs more than its contents.
+int upload_ints(chfsi_op* op, const std::vector<std::pair<const std::vector<int32_t>*, const int32_t**>>& tables) {
+  std::vector<int32_t> all;
+  std::vector<size_t> at;
+  for (const auto& t : tables) {
+    at.push_back(all.size());
+    all.insert(all.end(), t.first->begin(), t.first->end());
+    all.resize((all.size() + 63) / 64 * 64);
+  }
+  int32_t* d = nullptr;
+  CHECK(upload(op, all, &d));
+  for (size_t i = 0; i < tables.size(); ++i) *tables[i].second = d + at[i];
+  return 0;
+}
+
+// A table (a multiple of 64 entries) in double and in single precision, rounded
+// on the device: the second copy over the host link and the host's conversion
+// were a fifth of the operator build.
 int upload_both(chfsi_op* op, const std::vector<double>& v, void** out64, void** out32) {
   double* d = nullptr;
   CHECK(upload(op, v, &d));
   *out64 = d;
   *out32 = nullptr;
-  if (v.size() % 64 != 0) {
-    float* f = nullptr;
-    CHECK(upload(op, std::vector<float>(v.begin(), v.end()), &f));
-    *out32 = f;
-  } else if (!v.empty()) {
-    void* p = nullptr;
-    if (hipMalloc(&p, v.size() * sizeof(float)) != hipSuccess)
-      return fail(op->ctx, CHFSI_ENOMEM, "hipMalloc of operator table failed");
-    op->allocs.push_back(p);
-    HIP_TRY(op->ctx, launch_convert(p, 64, CHFSI_F32, d, 64, CHFSI_F64, static_cast<int64_t>(v.size() / 64), 64,
-                                    op->ctx->stream));
-    *out32 = p;
-  }
+  if (v.empty()) return 0;
+  void* p = nullptr;
+  if (hipMalloc(&p, v.size() * sizeof(float)) != hipSuccess)
+    return fail(op->ctx, CHFSI_ENOMEM, "hipMalloc of operator table failed");
+  op->allocs.push_back(p);
+  HIP_TRY(op->ctx, launch_convert(p, 64, CHFSI_F32, d, 64, CHFSI_F64, static_cast<int64_t>(v.size() / 64), 64,
+                                  op->ctx->stream));
+  *out32 = p;
   return 0;
 }
 
-// The owner cells' projector values, from the uploaded pair tables.
-int build_own_table(chfsi_op* op) {
+// The owner cells' index tables, and their projector values from the uploaded
+// pair tables.
+int build_own_tables(chfsi_op* op) {
   const HostTables& t = op->t;
+  op->nown_cells = static_cast<int>(t.own_cell.size());
+  op->nown_pairs = static_cast<int>(t.own_atom.size());
+  const int32_t* pairs = nullptr;
+  CHECK(upload_ints(op, {{&t.own_cell, &op->own_cell}, {&t.own_ptr, &op->own_ptr}, {&t.own_atom, &op->own_atom},
+                         {&t.atom_pair_ptr, &op->atom_pair_ptr}, {&t.atom_pair, &op->atom_pair},
+                         {&t.own_pair, &pairs}}));
   const size_t n = op->nown_pairs * own_table_entries(t.p, t.cplx);
   if (n == 0) return 0;
-  int32_t* pairs = nullptr;
-  CHECK(upload(op, t.own_pair, &pairs));
-  for (void** p : {&op->own_val64, &op->own_val32}) {
-    if (hipMalloc(p, n * (p == &op->own_val64 ? 8 : 4)) != hipSuccess)
-      return fail(op->ctx, CHFSI_ENOMEM, "hipMalloc of operator table failed");
-    op->allocs.push_back(*p);
-  }
+  void* v = nullptr;
+  if (hipMalloc(&v, n * 12) != hipSuccess) return fail(op->ctx, CHFSI_ENOMEM, "hipMalloc of operator table failed");
+  op->allocs.push_back(v);
+  op->own_val64 = v;
+  op->own_val32 = static_cast<double*>(v) + n;
   HIP_TRY(op->ctx, launch_own_table(pairs, op->nown_pairs, t.p, t.mpad, static_cast<const double*>(op->pair_re64),
                                     static_cast<const double*>(op->pair_im64), static_cast<double*>(op->own_val64),
                                     static_cast<float*>(op->own_val32), op->ctx->stream));
@@ -1863,9 +1879,15 @@ int chfsi_op_build(chfsi_ctx* ctx, const chfsi_system* sys, chfsi_op** out) {
       swizzle_cell_matrix(t.cell_im.data(), t.mcell, t.mpad, sw.data());
       if ((rc = upload_both(op.get(), sw, &op->Ai64, &op->Ai32)) < 0) break;
     }
-    std::vector<double> ts(kTensorTab);
+    // the 1D factors, followed by themselves in single precision
+    std::vector<double> ts(kTensorTab + kTensorTab / 2);
     pack_tensor_tables(t.p, t.ts_K.data(), t.ts_S.data(), t.ts_m.data(), ts.data());
-    if ((rc = upload_both(op.get(), ts, &op->ts_tab64, &op->ts_tab32)) < 0) break;
+    const std::vector<float> ts32(ts.begin(), ts.begin() + kTensorTab);
+    std::memcpy(ts.data() + kTensorTab, ts32.data(), kTensorTab * sizeof(float));
+    double* tsd;
+    if ((rc = upload(op.get(), ts, &tsd)) < 0) break;
+    op->ts_tab64 = tsd;
+    op->ts_tab32 = tsd + kTensorTab;
     if ((rc = upload(op.get(), t.vdiag, &op->vdiag)) < 0) break;
     if ((rc = upload(op.get(), t.dscale, &op->dscale)) < 0) break;
     if (t.has_proj) {
@@ -1887,13 +1909,6 @@ int chfsi_op_build(chfsi_ctx* ctx, const chfsi_system* sys, chfsi_op** out) {
       if ((rc = upload(op.get(), ca, &op->chunk_atom)) < 0) break;
       if ((rc = upload(op.get(), cb, &op->chunk_begin)) < 0) break;
       if ((rc = upload(op.get(), acp, &op->atom_chunk_ptr)) < 0) break;
-      if ((rc = upload(op.get(), t.own_cell, &op->own_cell)) < 0) break;
-      if ((rc = upload(op.get(), t.own_ptr, &op->own_ptr)) < 0) break;
-      if ((rc = upload(op.get(), t.own_atom, &op->own_atom)) < 0) break;
-      if ((rc = upload(op.get(), t.atom_pair_ptr, &op->atom_pair_ptr)) < 0) break;
-      if ((rc = upload(op.get(), t.atom_pair, &op->atom_pair)) < 0) break;
-      op->nown_cells = static_cast<int>(t.own_cell.size());
-      op->nown_pairs = static_cast<int>(t.own_atom.size());
       if ((rc = upload(op.get(), t.pair_ptr, &op->pair_ptr)) < 0) break;
       if ((rc = upload(op.get(), t.pair_atom, &op->pair_atom)) < 0) break;
       op->npairs = static_cast<int64_t>(t.pair_atom.size());
@@ -1901,7 +1916,7 @@ int chfsi_op_build(chfsi_ctx* ctx, const chfsi_system* sys, chfsi_op** out) {
       if (t.cplx) {
         if ((rc = upload_both(op.get(), t.pair_im, &op->pair_im64, &op->pair_im32)) < 0) break;
       }
-      if ((rc = build_own_table(op.get())) < 0) break;
+      if ((rc = build_own_tables(op.get())) < 0) break;
     }
     if (hipStreamSynchronize(ctx->stream) != hipSuccess) rc = fail(ctx, CHFSI_EHIP, "operator table upload failed");
   } while (0);

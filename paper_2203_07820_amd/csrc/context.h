@@ -101,11 +101,11 @@ struct chfsi_op {
   void* pair_re32 = nullptr; void* pair_im32 = nullptr;
   void* ts_tab64 = nullptr; void* ts_tab32 = nullptr;   // 1D factors of the cell matrix (tensor-product path)
   // owned-node projector tables (nonlocal update)
-  int32_t* own_cell = nullptr;
-  int32_t* own_ptr = nullptr;
-  int32_t* own_atom = nullptr;
-  int32_t* atom_pair_ptr = nullptr;
-  int32_t* atom_pair = nullptr;
+  const int32_t* own_cell = nullptr;
+  const int32_t* own_ptr = nullptr;
+  const int32_t* own_atom = nullptr;
+  const int32_t* atom_pair_ptr = nullptr;
+  const int32_t* atom_pair = nullptr;
   void* own_val64 = nullptr; void* own_val32 = nullptr;
   int nown_cells = 0, nown_pairs = 0;
   double* d_x1d = nullptr;      // node coordinates along one axis (features)
