@@ -2950,8 +2950,9 @@ int subspace_small_batched(chfsi_ctx* ctx, const std::vector<int>& idx, chfsi_op
                                static_cast<int>(Nq * cf), static_cast<int>(Nq * cf), true, ctx->stream));
     const int prec = op->t.cplx ? CHFSI_C128 : CHFSI_F64;
     double* W = at(oW[k]);
-    HIP_TRY(ctx, launch_fill(W, op->t.M, Nq * cf, Nq * cf, prec, ctx->stream));
-    CHECK(hx_step(op, prec, tensor_single(op, prec, Nq, Nq), X2, Nq, nullptr, 0, W, Nq, Nq, 1.0, 0.0, 0.0, false));
+    const bool tensor = tensor_single(op, prec, Nq, Nq);
+    if (!tensor) HIP_TRY(ctx, launch_fill(W, op->t.M, Nq * cf, Nq * cf, prec, ctx->stream));
+    CHECK(hx_step(op, prec, tensor, X2, Nq, nullptr, 0, W, Nq, Nq, 1.0, 0.0, 0.0, false));
     double* Hh = at(oH[k]);
     CHECK(gram(op, X2, Nq, W, Nq, Nq, &Hh));
   }
