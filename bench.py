@@ -15,7 +15,7 @@ Prints one JSON line.  ``value`` is the pass's algorithmic flop rate
 (cell products, nonlocal products and subspace GEMMs counted without
 padding, the cell products as dense ones) in GFLOP/s; ``ms_per_step`` is the
 pass time.  H~.X applies the cell products as tensor products of 1D matrices,
-a twelfth of the dense operations at p = 6, so the flop rate compares runs of
+a ninth of the dense operations at p = 6, so the flop rate compares runs of
 this benchmark and is no share of the MFMA peak.  The ``roofline`` object
 reports H~.X (the tensor-product kernel and the nonlocal update behind it)
 against the HBM peak: X_k and X_{k-1} read once and X_{k+1} written once per
@@ -28,7 +28,7 @@ host cores.
 Other workloads (``--workload``), each printing one JSON line of its own:
 c2 (time to Delta E <= 1e-6 Ha at N = 1024 for FP64, FP32, BF16 and the
 mixed schedule), c3 (32 batched complex k-point problems, sequential vs
-persistent launch vs hipGraph, complex128 vs complex64), c4 (learned warm
+common launches vs hipGraph, complex128 vs complex64), c4 (learned warm
 start: training on solver output, passes saved on held-out configurations)
 kernels (one 128-column filter step per precision), density (electron
 density of the c2 block at the nodes and at the Gauss points of every cell,
@@ -506,11 +506,9 @@ def run_c2(args):
 def run_c3(args):
     """Batched uneven k-point solves: 8 periodic p = 5 systems x 4 Monkhorst-Pack
     k-points (32 complex Bloch operators).  Per pass: each problem solved on
-    its own (complex128) against one batched solve (persistent launch per
-    Chebyshev step, without and with the hipGraph) in complex128 and complex64,
-    tile shapes from the autotuner."""
-    import tempfile
-
+    its own (complex128) against one batched solve (common launches per
+    Chebyshev step, without and with the hipGraph) in complex128 and
+    complex64."""
     import numpy as np
     import torch
 
@@ -548,13 +546,6 @@ def run_c3(args):
 
     def per_pass_ms(h):
         return float(np.median(np.diff(h["time_ms"])))
-
-    tune_path = os.path.join(tempfile.gettempdir(), "chfsi_tuning_c3.json")
-    tuning = {}
-    for name, prec in (("c128", lib.C128), ("c64", lib.C64)):
-        t1 = time.perf_counter()
-        tuning[name] = ctx.autotune(5, prec, B, cache_json=tune_path)
-        log(f"# autotune {name}: {tuning[name]} ({time.perf_counter() - t1:.1f}s)")
 
     modes = {}
     # each problem on its own, complex128 (cell-kernel launches timed with HIP events)
@@ -622,7 +613,6 @@ def run_c3(args):
         "speedup_c64_vs_c128": pm / modes["batched_graph_c64"]["pass_ms"],
         "max_dtheta_batched_vs_sequential": d_seq,
         "max_dtheta_c64_vs_c128_after_same_passes": d_c64,
-        "tuning": tuning,
     }
     print(json.dumps(out), flush=True)
 

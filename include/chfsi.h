@@ -467,7 +467,7 @@ int chfsi_scf_kpoints(chfsi_ctx* ctx, int32_t nk, chfsi_op* const* ops, void* co
                       int32_t maxit, double* rho, double* const* theta, double* mu_out, double* res_hist,
                       int32_t* iters);
 
-/* ---- batched filter (many operators, one persistent launch per step) -------
+/* ---- batched filter (many operators, common launches per step) -------------
  * Applies the filter of chfsi_filter() to n independent blocks at once:
  * block q is X[q] (device, double / complex double, ncols[q] columns, ld[q])
  * of operator ops[q] with interval a[q], b[q], aL[q] (aL < a < b).  All
@@ -476,13 +476,14 @@ int chfsi_scf_kpoints(chfsi_ctx* ctx, int32_t nk, chfsi_op* const* ops, void* co
  * columns (<= 0: all) of every problem are filtered together: each
  * Chebyshev step of a round is one launch of the tensor-product kernel over
  * all problems, and two of the nonlocal kernels where there are projectors; if
- * an operator has cell matrices of its own, one launch of a persistent kernel
- * whose work list concatenates every problem's (cell, column tile) items.  The
- * per-problem arguments and recurrence scalars come from device tables.  use_graph != 0
- * captures the whole sequence into a hipGraph (kept in the context and
- * replayed while the operators, buffers and shapes stay the same).  Grid
- * shape of the persistent kernel from chfsi_autotune() when tuned, else one
- * workgroup per item.  Results equal chfsi_filter() on each block up to the
+ * an operator has cell matrices of its own (or a block planes of 2 GB or more),
+ * one launch of the dense cell kernel, whose work list concatenates every
+ * problem's (cell, column tile) items.  The per-problem arguments and recurrence
+ * scalars come from device tables.  use_graph != 0 captures the whole sequence
+ * into a hipGraph (kept in the context and replayed while the operators, buffers
+ * and shapes stay the same).  Grid shape of the dense kernel from
+ * chfsi_autotune() or chfsi_load_tuning() when tuned, else one workgroup per
+ * item; it has no effect on the tensor-product kernel.  Results equal chfsi_filter() on each block up to the
  * order of sums (on the tensor-product path: of the projections).
  * Asynchronous. */
 int chfsi_filter_batched(chfsi_ctx* ctx, int32_t n, chfsi_op* const* ops, void* const* X, const int64_t* ncols,
@@ -521,7 +522,8 @@ int chfsi_solve_batched(chfsi_ctx* ctx, int32_t n, chfsi_op* const* ops, const c
  * and, when cache_json is not NULL, merges it into that JSON file (read
  * first, then rewritten).  Synchronous.  chfsi_load_tuning() reads such a
  * file into the context (an entry without "col_tile" takes the default
- * rule); chfsi_get_tuning() returns the shape the batched launch will use:
+ * rule); chfsi_get_tuning() returns the shape that a batch of the dense cell
+ * kernel takes (other batches take no shape):
  * grid_per_cu, contiguous, col_tile (64 or 32; 0 = the default rule, 32 when
  * every block has at most 32 real columns, else 64) and the tuned time in ms
  * (0 when untuned); every output pointer is nullable.  Untuned single-problem
@@ -585,10 +587,9 @@ int chfsi_initial_block(chfsi_op* op, chfsi_mlp* net, uint64_t seed, void* X, in
  * so the order in which the up to 8 cells sharing a node add into it depends
  * on workgroup timing and the result can differ from run to run in the last
  * bits.  chfsi_set_deterministic(ctx, 1) takes the tensor-product kernel for
- * those small products too and runs the dense kernel of every other H~.X of
- * the context (chfsi_apply, chfsi_apply_noalloc, the filter, the solvers; the
- * batched filter and solve then run problem by problem) colour class by colour
- * class: along each axis the cells take colours 0, 1, 0, 1, ...
+ * those small products too and runs every H~.X that is left to the dense kernel
+ * (in chfsi_apply, chfsi_apply_noalloc, the filter, the solvers; the batched
+ * filter and solve then run problem by problem) colour class by colour class: along each axis the cells take colours 0, 1, 0, 1, ...
  * (and 2 for the last cell of an odd side), a class is a triple of axis
  * colours, no two cells of one class share a node, and the classes run in a
  * fixed order, one launch each (8 launches per H~.X for an even number of
@@ -614,7 +615,7 @@ int chfsi_set_deterministic(chfsi_ctx* ctx, int32_t enable);
  * summed duration (ms), the number of products and their summed algorithmic
  * flops since the last reset (reset != 0 clears the counters after reading).
  * The flops are those of the dense cell products, in whatever form they are
- * made: the tensor-product kernel does about a twelfth of them at p = 6. */
+ * made: the tensor-product kernel does about a ninth of them at p = 6. */
 int chfsi_set_timing(chfsi_ctx* ctx, int32_t enable);
 int chfsi_kernel_time(chfsi_ctx* ctx, double* total_ms, int64_t* launches, double* flops, int32_t reset);
 

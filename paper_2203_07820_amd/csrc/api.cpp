@@ -1294,11 +1294,12 @@ int batched_tensor_filter(chfsi_ctx* ctx, const std::vector<BItem>& items, int m
 
 // Filters every item's block X (all columns, in rounds of `block` columns)
 // with degree m on its own [a, b], aL: by the tensor-product kernels
-// (batched_tensor_filter), or, where an operator has its own cell matrices or
-// a launch shape is forced, by one persistent launch of the dense cell kernel
-// per Chebyshev step (cell_hx_batched_kernel).  16 complex boxes of 3^3 to 6^3
-// cells, p = 5, degree 20: 6.7 ms by the former, 14.4 ms by the latter.  The
-// per-item recurrence scalars live in device descriptor tables written before
+// (batched_tensor_filter), or, where one of the operators cannot take them (cell
+// matrices of its own, a block with planes of 2 GB) and in the autotuner's timing
+// runs (`force`), by one launch of the dense cell kernel per Chebyshev step
+// (cell_hx_batched_kernel), to which alone loaded and tuned launch shapes apply.
+// 16 complex boxes of 3^3 to 6^3 cells, p = 5, degree 20: 5.9 ms by the former,
+// 14.4 ms by the latter.  The per-item recurrence scalars live in device descriptor tables written before
 // the launch, so with use_graph the whole sequence is captured once into a
 // hipGraph and replayed while the tables change.
 int batched_filter(chfsi_ctx* ctx, const std::vector<BItem>& items, int m, int prec, int64_t block,

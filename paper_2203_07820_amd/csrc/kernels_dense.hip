@@ -780,7 +780,9 @@ hipError_t rotate_t(const T* X, int64_t ldx, const T* Z, int64_t ldz, T* C, int6
   // 256: 1.03 and 1.15, 512: 4.2 and 4.5, 1024: 15.6 and 16.5; 216,000 x 160 by
   // 32 columns and 4096 x 32 by 32 the rows take half the time.  Triangular: 128
   // columns 0.30 and 0.28, 256: 0.82 and 0.68, 512: 2.59 and 2.49, 1024: 8.9 and
-  // 8.7 ms.
+  // 8.7 ms.  Full Z of 65, 96 and 127 columns, tiles against rows: 193 and 242,
+  // 223 and 285, 313 and 368 us on 373,248 rows; 20 and 13, 23 and 16, 29 and 20 us
+  // on 13,824, where 108 tiles leave half of the device idle.
   const bool rows = upper || ((N2 + 63) / 64 % 2 == 1 && N2 <= 512);
   if (!rows) {
     const int64_t gt = (M + kTM - 1) / kTM;

@@ -4,7 +4,8 @@
 // defined on its entries, per-cell matrices (quadrature potential), blocks
 // with planes of 2 GB or more, and single products on small meshes of order 2
 // and 3.  Everything else takes the tensor-product kernel
-// (kernels_tensor.hip), 2.6 times faster in FP64 at p = 6.
+// (kernels_tensor.hip) and the nonlocal update behind it, twice as fast in an FP64
+// filter at p = 6.
 //
 // One workgroup owns one hexahedral cell and a 64-wide tile of columns.  It
 //   1. reads the cell's nodal rows X^c (node-major, 64 contiguous values per

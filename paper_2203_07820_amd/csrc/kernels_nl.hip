@@ -269,8 +269,10 @@ hipError_t nl_launch(const NlLaunch& L, hipStream_t s) {
 // 16 the projector values are read twice as often (3 % of a filter), with 64
 // two waves per SIMD fit instead of four (3 % on the 12^3 box).  Requesting a
 // tile's projector values together takes 3 % off the filter on the 12^3 box;
-// complex FP64 and the batched kernel would spill registers for it and are 6-8 %
-// slower that way.
+// complex FP64 and the batched kernel are 6-8 % slower that way.  The batched
+// kernel in FP64, real and complex, has 20 to 44 bytes per lane in scratch
+// memory at p = 4..7 as it is (128 registers; its arguments come from a table),
+// the single-problem one none (114 to 121).
 constexpr int kNlGroups = 2;   // groups of 16 real columns per wave
 typedef double nd4 __attribute__((ext_vector_type(4)));
 typedef float nf4 __attribute__((ext_vector_type(4)));

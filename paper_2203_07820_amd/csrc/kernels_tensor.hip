@@ -10,12 +10,13 @@
 // degree p exactly except that of the two leading terms, so the consistent
 // mass is the lumped one less a rank-one term,
 //   M = diag(1/2, 1, .., 1, 1/2) - m m^T,  m_i ~ sqrt(w_i) P_p(x_i),
-// whose diagonal assembles to the identity.  Applied axis by axis, A takes 3
-// products with (p+1) x (p+1) matrices and 4 rank-one ones per cell instead of
-// one product with a (p+1)^3 x (p+1)^3 matrix: about 2 (3 (p+1) + 8) operations
-// per cell node and column instead of 2 (p+1)^3, 12 times fewer at p = 6.  That leaves
-// memory as the bound.  The 1D products are too small for MFMA tiles (and
-// FP64 runs at the same rate on the vector units).
+// whose diagonal assembles to the identity.  Applied axis by axis, A takes 5
+// products with (p+1) x (p+1) matrices per cell (B_x, three in y: M twice and
+// B_y, and B_z), and M in x and in z by its rank-one form, instead of one product
+// with a (p+1)^3 x (p+1)^3 matrix: about 2 (5 (p+1) + 5) operations per cell node
+// and column instead of 2 (p+1)^3, 8.6 times fewer at p = 6 (complex data: B by
+// two products).  That leaves memory as the bound.  The 1D products are too small
+// for MFMA tiles (and FP64 runs at the same rate on the vector units).
 //
 // Each node is computed by one thread and written once: nothing is zeroed
 // beforehand, no atomics are needed, every node's sum has a fixed order.  A
@@ -34,10 +35,12 @@
 // The nonlocal term is added by nl_update_kernel.
 // Bound by memory: on 24^3 cells, p = 6, 128 columns, FP64, a filter step moves
 // 11.3 GB (9.2 GB needed) in 3.03 ms, where a three-stream add over as much
-// runs at 5.5 TB/s; 7.9 ms by the dense cell kernel, which moved 17.5 GB.  The
-// first step (no X_{k-1}): 2.56 ms; FP32 1.32 ms (5.1 dense); 12^3 cells, p = 5,
-// 160 columns: 0.257 ms (0.76 dense); 20^3 cells, p = 5, complex FP64: 1.98 ms
-// (7.1 dense).
+// runs at 5.5 TB/s.  The first step (no X_{k-1}): 2.56 ms; FP32 1.32 ms; 12^3
+// cells, p = 5, 160 columns: 0.257 ms; 20^3 cells, p = 5, complex FP64: 1.98 ms.
+// All without the nonlocal term.  A whole step with the update and its sums, and
+// one by the dense cell kernel with the projections before it: 4.19 and 8.60 ms;
+// 0.42 and 0.88 ms on the 12^3 cells; a complex product of its own 3.15 and
+// 7.66 ms.
 // LDS is double buffered with one barrier per plane; a chunk starts with the
 // cell below it, whose top plane it shares.
 #include <hip/hip_runtime.h>
