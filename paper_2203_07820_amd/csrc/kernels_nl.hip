@@ -269,10 +269,14 @@ hipError_t nl_launch(const NlLaunch& L, hipStream_t s) {
 // 16 the projector values are read twice as often (3 % of a filter), with 64
 // two waves per SIMD fit instead of four (3 % on the 12^3 box).  Requesting a
 // tile's projector values together takes 3 % off the filter on the 12^3 box;
-// complex FP64 and the batched kernel are 6-8 % slower that way.  The batched
-// kernel in FP64, real and complex, has 20 to 44 bytes per lane in scratch
-// memory at p = 4..7 as it is (128 registers; its arguments come from a table),
-// the single-problem one none (114 to 121).
+// complex FP64 and the batched kernel are 6-8 % slower that way.
+// The atoms' terms are summed from zero and the sum is added to the row.  With
+// the row as the MFMAs' accumulator it would be rounded in each of their four
+// steps, at its own size: a degree-10 FP32 filter with three atoms over the box
+// then was off by 4.6e-7 (p = 7; the dense kernel: 4.0e-7), now by 2.8e-7.  In the
+// batched FP64 kernels, whose registers do not hold the sums, every atom's term
+// is added on its own.  FP64 takes all 128 registers and up to 16 bytes per lane
+// of scratch memory (real, p = 2, 6 and 7), batched up to 28 (complex, p = 7).
 constexpr int kNlGroups = 2;   // groups of 16 real columns per wave
 typedef double nd4 __attribute__((ext_vector_type(4)));
 typedef float nf4 __attribute__((ext_vector_type(4)));
@@ -303,14 +307,20 @@ __device__ __forceinline__ float nl_rot(float v, int lane) {
   return (lane & 1) ? -o : o;
 }
 
-template <int P, typename T, bool CPLX, bool TOGETHER>
+// The index tables and a batch's descriptors are read with scalar loads: they
+// are the same for a whole wave, and no vector registers are left for them.
+template <typename T> using cptr = const __attribute__((address_space(4))) T*;
+template <typename T> __device__ __forceinline__ cptr<T> to_const(const T* p) { return (cptr<T>)p; }
+
+template <int P, typename T, bool CPLX, bool TOGETHER, bool ACROSS>
 __device__ __forceinline__ void nl_update_item(const NlUpdate& a, const int item, const int ctile,
                                                const int32_t* noff, const int part_z = 0, const int parts = 1) {
     constexpr int P3 = P * P * P, NT = (P3 + 15) / 16, CV = CPLX ? 2 : 1, NC = kNlGroups;
   typedef typename NlMma<T>::acc acc_t;
   const int lane = threadIdx.x % 64, q = lane / 16, cl = lane % 16;
-  const int cell = a.cells[item];
-  const int p0 = a.pair_ptr[item], np = a.pair_ptr[item + 1] - p0;
+  const auto pair_ptr = to_const(a.pair_ptr);
+  const int cell = to_const(a.cells)[item];
+  const int p0 = pair_ptr[item], np = pair_ptr[item + 1] - p0;
   const int nc = a.nc, n = nc * P;
   const int64_t base = static_cast<int64_t>(cell % nc) * P +
                        static_cast<int64_t>(n) * ((cell / nc) % nc * P + static_cast<int64_t>(n) * (cell / (nc * nc) * P));
@@ -338,28 +348,43 @@ __device__ __forceinline__ void nl_update_item(const NlUpdate& a, const int item
   };
   const gptr<const T> val = to_global(static_cast<const T*>(a.val)) + static_cast<int64_t>(p0) * NT * CV * 64;
   const gptr<const T> hp = to_global(static_cast<const T*>(a.hP));
-  const T al = static_cast<T>(a.alpha);
+  const T al = static_cast<T>(a.alpha), al_lo = static_cast<T>(a.alpha - static_cast<double>(al));
   T hb[4][NC];   // alpha h P of the first four atoms, B operands
   auto load_h = [&](int g, T (&h)[NC]) {
-    const gptr<const T> r = hp + (static_cast<int64_t>(a.pair_atom[p0 + g]) * 4 + q) * a.ldhp;
+    const gptr<const T> r = hp + (static_cast<int64_t>(to_const(a.pair_atom)[p0 + g]) * 4 + q) * a.ldhp;
 #pragma unroll
-    for (int c = 0; c < NC; ++c) h[c] = al * r[col[c]];
+    for (int c = 0; c < NC; ++c) {
+      const T v = r[col[c]];
+      h[c] = al * v;
+      if constexpr (sizeof(T) == 4) h[c] += al_lo * v;
+    }
   };
 #pragma unroll
-  for (int g = 0; g < 4; ++g)
+  for (int g = 0; g < 4; ++g) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) hb[g][c] = T(0);
     if (g < np) load_h(g, hb[g]);
+  }
   auto load_c = [&](int g, int t, T (&cv)[CV]) {
 #pragma unroll
     for (int v = 0; v < CV; ++v) cv[v] = val[((static_cast<int64_t>(g) * NT + t) * CV + v) * 64 + lane];
   };
-  auto add = [&](const T (&cv)[CV], const T (&h)[NC], Tile& u) {
+  // d += one atom's term at the tile's rows
+  auto term = [&](const T (&cv)[CV], const T h, acc_t& d) {
+    d = NlMma<T>::run(cv[0], h, d);
+    if constexpr (CPLX) d = NlMma<T>::run(cv[1], -nl_rot(h, lane), d);
+  };
+  auto add = [&](const acc_t& d, T (&y)[4]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) y[i] += d[i];
+  };
+  // one atom's term on its own
+  auto one = [&](const T (&cv)[CV], const T (&h)[NC], Tile& u) {
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      acc_t d = {u.y[c][0], u.y[c][1], u.y[c][2], u.y[c][3]};
-      d = NlMma<T>::run(cv[0], h[c], d);
-      if constexpr (CPLX) d = NlMma<T>::run(cv[1], -nl_rot(h[c], lane), d);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) u.y[c][i] = d[i];
+      acc_t d = {0, 0, 0, 0};
+      term(cv, h[c], d);
+      add(d, u.y[c]);
     }
   };
   acc_t pj[NC];   // projections: 16 columns x 4 projectors of 4 atoms
@@ -412,18 +437,43 @@ __device__ __forceinline__ void nl_update_item(const NlUpdate& a, const int item
       for (int g = 0; g < 4; ++g) load_c(g < np ? g : 0, t, cv[g]);
       load_p(0, t, b);
     }
+    if constexpr (TOGETHER) {
+      acc_t d[NC];
 #pragma unroll
-    for (int g = 0; g < 4; ++g)
-      if (g < np) {
-        if constexpr (!TOGETHER) load_c(g, t, cv[0]);
-        add(cv[TOGETHER ? g : 0], hb[g], u);
-      }
+      for (int c = 0; c < NC; ++c) d[c] = acc_t{0, 0, 0, 0};
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) term(cv[g], hb[g][c], d[c]);
+#pragma unroll
+      for (int c = 0; c < NC; ++c) add(d[c], u.y[c]);
+    } else if constexpr (ACROSS) {
+      acc_t d[NC];
+#pragma unroll
+      for (int c = 0; c < NC; ++c) d[c] = acc_t{0, 0, 0, 0};
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        if (g < np) {
+          load_c(g, t, cv[0]);
+#pragma unroll
+          for (int c = 0; c < NC; ++c) term(cv[0], hb[g][c], d[c]);
+        }
+#pragma unroll
+      for (int c = 0; c < NC; ++c) add(d[c], u.y[c]);
+    } else {
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        if (g < np) {
+          load_c(g, t, cv[0]);
+          one(cv[0], hb[g], u);
+        }
+    }
 #pragma unroll 1
     for (int g = 4; g < np; ++g) {
       T h[NC], c1[CV];
       load_h(g, h);
       load_c(g, t, c1);
-      add(c1, h, u);
+      one(c1, h, u);
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -482,33 +532,42 @@ __global__ void __launch_bounds__(256, 4) nl_update_kernel(const NlUpdate a) {
   __shared__ int32_t noff[(P * P * P + 15) / 16 * 16];
   nl_node_offsets<P>(a.nc, noff);
   const int item = __builtin_amdgcn_readfirstlane(blockIdx.x * kNlCells + threadIdx.x / 64);
-  if (item < a.ncells) nl_update_item<P, T, CPLX, !(CPLX && sizeof(T) == 8)>(a, item, blockIdx.y, noff, blockIdx.z, gridDim.z);
+  if (item < a.ncells) nl_update_item<P, T, CPLX, !(CPLX && sizeof(T) == 8), true>(a, item, blockIdx.y, noff, blockIdx.z, gridDim.z);
 }
 
 // The update of many problems (batched filter): descriptors in device memory.
+__device__ __forceinline__ NlUpdate load_update(const NlUpdate* p) {
+  struct Words { uint64_t w[sizeof(NlUpdate) / 8]; } v;
+  static_assert(sizeof(Words) == sizeof(NlUpdate), "whole words");
+  const cptr<uint64_t> s = to_const(reinterpret_cast<const uint64_t*>(p));
+#pragma unroll
+  for (unsigned i = 0; i < sizeof(NlUpdate) / 8; ++i) v.w[i] = s[i];
+  return __builtin_bit_cast(NlUpdate, v);
+}
+
 template <int P, typename T, bool CPLX>
 __global__ void __launch_bounds__(256, 4)
 nl_update_batched_kernel(const NlUpdate* __restrict__ d, const int64_t* __restrict__ cell_off, const int nprob) {
   __shared__ int32_t noff[(P * P * P + 15) / 16 * 16];
   const int q = __builtin_amdgcn_readfirstlane(problem_of(cell_off, nprob, blockIdx.x));
-  const NlUpdate a = d[q];
+  const NlUpdate a = load_update(d + q);
   if (static_cast<int>(blockIdx.y) * 16 * kNlGroups >= a.nreal) return;
   nl_node_offsets<P>(a.nc, noff);
   const int item =
       __builtin_amdgcn_readfirstlane(static_cast<int>(blockIdx.x - cell_off[q]) * kNlCells + threadIdx.x / 64);
-  if (item < a.ncells) nl_update_item<P, T, CPLX, false>(a, item, blockIdx.y, noff);
+  if (item < a.ncells) nl_update_item<P, T, CPLX, false, sizeof(T) == 4>(a, item, blockIdx.y, noff);
 }
 
 // hP[atom][m] = h sum over the atom's pairs of their partial projections, 64
 // columns per workgroup: 8 waves take every 8th pair, their sums are added in
-// a fixed order.
+// a fixed order, in double (hundreds of pairs per atom).
 template <typename T>
 __device__ __forceinline__ void nl_pair_reduce_item(const NlUpdate& a, const int am, const int jblk) {
-  __shared__ T red[8][64];
+  __shared__ double red[8][64];
   const int at = am / 4, m = am % 4;
   const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
   const int64_t j = jblk * 64 + lane;   // ldhp is a multiple of 64
-  T s = T(0);
+  double s = 0.0;
   if (j < a.nreal) {
     const gptr<const T> part = to_global(static_cast<const T*>(a.part)) + j + m * a.ldhp;
     const gptr<const int32_t> list = to_global(a.atom_pair);
@@ -521,7 +580,7 @@ __device__ __forceinline__ void nl_pair_reduce_item(const NlUpdate& a, const int
   if (wave != 0) return;
 #pragma unroll
   for (int w = 1; w < 8; ++w) s += red[w][lane];
-  to_global(static_cast<T*>(a.hP))[static_cast<int64_t>(am) * a.ldhp + j] = s * static_cast<T>(a.hcoef[am]);
+  to_global(static_cast<T*>(a.hP))[static_cast<int64_t>(am) * a.ldhp + j] = static_cast<T>(s * a.hcoef[am]);
 }
 
 template <typename T>

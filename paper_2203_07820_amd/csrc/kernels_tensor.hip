@@ -46,6 +46,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 
 #include "device_util.h"
 #include "internal.h"
@@ -80,7 +81,9 @@ struct TsArgs {
   const T* tab;                 // 1D factors
   int ncols, nc, nz;            // real columns, cells per side, cells per chunk in z
   int has_prev;
-  T ak, bk, c, ikap;            // alpha kappa, beta / (alpha kappa), c, 1 / kappa
+  // alpha kappa and beta / (alpha kappa), each in two parts; c / kappa, 1 / kappa
+  T ak, ak_lo, bk, bk_lo;
+  double ck, ikap;
   T sx, sy, sz;                 // k_d h (complex operators)
 };
 
@@ -434,8 +437,11 @@ __device__ __forceinline__ void ts_consume(const cptr<TsArgs<T>> args, const TsT
     const cptr<TsArgs<T>> A = reload(args);
 #pragma unroll
     for (int j = 0; j < JN; ++j) {
-      os[j] = ((static_cast<T>(vo[j]) - A->c) * A->ikap) * xo[j];
+      const double w = vo[j] * A->ikap - A->ck;
+      os[j] = static_cast<T>(w) * xo[j];
+      if constexpr (sizeof(T) == 4) os[j] += static_cast<T>(w - static_cast<T>(w)) * xo[j];
       os[j] -= A->bk * xp[j];
+      os[j] -= A->bk_lo * xp[j];
     }
   };
   auto own_add = [&](int k) __attribute__((always_inline)) {
@@ -450,14 +456,14 @@ __device__ __forceinline__ void ts_consume(const cptr<TsArgs<T>> args, const TsT
   auto emit = [&](int zc) __attribute__((always_inline)) {
     const cptr<TsArgs<T>> A = reload(args);
     const uint32_t lt = static_cast<uint32_t>(A->ldt * ES);
-    const T ak = A->ak;
+    const T ak = A->ak, ak_lo = A->ak_lo;
     if (ok) {
 #pragma unroll
       for (int k = 0; k < P; ++k) {
         const __amdgpu_buffer_rsrc_t r = plane_rsrc(A->Tg, n2 * A->ldt, zc * P + k);
 #pragma unroll
         for (int j = 0; j < JN; ++j) {
-          const V v = ak * acc[k][j];
+          const V v = ak * acc[k][j] + ak_lo * acc[k][j];
           if constexpr (CL == 1) {
             bs(v, r, vt, j * n * lt);
           } else {
@@ -594,10 +600,18 @@ int64_t ts_pack(const TensorLaunch& L, double share, TsArgs<T>& a) {
   a.nc = L.nc;
   a.tab = static_cast<const T*>(L.tab);
   a.has_prev = L.Xp != nullptr;
-  a.ak = static_cast<T>(L.alpha / (L.h * L.h));
-  a.bk = static_cast<T>(L.beta / (L.alpha / (L.h * L.h)));
-  a.c = static_cast<T>(L.c);
-  a.ikap = static_cast<T>(L.h * L.h);
+  // the scalars of the recurrence, divided by alpha kappa.  Rounded once, each of
+  // them would be another polynomial, the same way at every node and in every
+  // step: up to 9e-7 of a degree-10 filter in single precision, where the
+  // roundings of its sums come to 3e-7.  The second part holds what the first
+  // one leaves; (V - c) / kappa is formed in double and applied in two parts.
+  const double hh = L.h * L.h, bh = L.beta * hh;
+  a.ikap = hh;
+  a.ck = L.c * hh;
+  a.ak = static_cast<T>(L.alpha / hh);
+  a.ak_lo = static_cast<T>(std::fma(-static_cast<double>(a.ak), hh, L.alpha) / hh);
+  a.bk = static_cast<T>(bh / L.alpha);
+  a.bk_lo = static_cast<T>((std::fma(-static_cast<double>(a.bk), L.alpha, bh) + std::fma(L.beta, hh, -bh)) / L.alpha);
   a.sx = static_cast<T>(L.kh[0]);
   a.sy = static_cast<T>(L.kh[1]);
   a.sz = static_cast<T>(L.kh[2]);
