@@ -34,11 +34,11 @@
 //   planes are stored, in place over X_{k-1} in the filter.
 // The nonlocal term is added by nl_update_kernel.
 // Bound by memory: on 24^3 cells, p = 6, 128 columns, FP64, a filter step moves
-// 11.3 GB (9.2 GB needed) in 3.03 ms, where a three-stream add over as much
-// runs at 5.5 TB/s.  The first step (no X_{k-1}): 2.56 ms; FP32 1.32 ms; 12^3
-// cells, p = 5, 160 columns: 0.257 ms; 20^3 cells, p = 5, complex FP64: 1.98 ms.
+// 11.2 GB (9.2 GB needed) in 3.05 ms, where a three-stream add over as much
+// runs at 5.5 TB/s.  The first step (no X_{k-1}): 2.56 ms; FP32 1.34 ms; 12^3
+// cells, p = 5, 160 columns: 0.258 ms; 20^3 cells, p = 5, complex FP64: 1.98 ms.
 // All without the nonlocal term.  A whole step with the update and its sums, and
-// one by the dense cell kernel with the projections before it: 4.19 and 8.60 ms;
+// one by the dense cell kernel with the projections before it: 4.20 and 8.60 ms;
 // 0.42 and 0.88 ms on the 12^3 cells; a complex product of its own 3.15 and
 // 7.66 ms.
 // LDS is double buffered with one barrier per plane; a chunk starts with the
